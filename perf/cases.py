@@ -225,7 +225,9 @@ class _Range:
 
 def _view(s: dict, address: int, n: int) -> torch.Tensor:
     if (address, n) not in s["views"]:
-        s["views"][address, n] = torch.as_tensor(_Range(address, n), device="cuda")
+        view = torch.as_tensor(_Range(address, n), device="cuda")
+        view.owner = s["server"]   # the memory is the server's: it lives as long as the view
+        s["views"][address, n] = view
     return s["views"][address, n]
 
 
