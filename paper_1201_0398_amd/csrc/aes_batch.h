@@ -42,11 +42,13 @@ constexpr uint32_t kCbcGroupMsgs = 16;
 // followed by 64 equivalent-inverse-cipher words.
 constexpr uint32_t kSchedWords = 128;
 
-// Device bytes of a launch's counters: 2 queue counters, one scratch flag per
-// workgroup (at most 1024 workgroups), then the count of workgroups that have
-// finished.  The counters must be zero before the first launch; the last
-// workgroup of every launch zeroes the queue counters and the count again.
+// Device bytes of a launch's counters, in words: queue q's count of pulled
+// tiles at word 32 * q and the count of workgroups that have finished at
+// kExitWord, each on a 128-byte line of its own.  The counters must be zero
+// before the first launch; the last workgroup of every launch zeroes them
+// again.
 constexpr size_t kCounterBytes = 4 * (2 + 1024) + 56;
+constexpr uint32_t kQueueStride = 32;
 constexpr uint32_t kExitWord = 2 + 1024;
 
 struct BatchTotals {
@@ -65,7 +67,7 @@ struct BatchLaunch {
     const DevMsg *msgs;
     const Tile *tiles[2];
     uint32_t n_tiles[2];
-    uint32_t *counters;      // kCounterBytes, zero before the launch (see kCounterBytes)
+    uint32_t *counters;      // kCounterBytes, zero before the launch
     const uint8_t *keys;     // raw keys (expanded on the device), or
     const uint32_t *sched;   // resident schedules (kSchedWords per slot)
     const uint8_t *in;
@@ -75,7 +77,7 @@ struct BatchLaunch {
     const Tile *cbc_groups;    // the groups, longest first (own launch)
     uint4 *cbc_dummy;          // 16 scratch bytes for stores with nothing to store
     uint32_t n_cbc_groups;
-    int n_cu;
+    int n_cu;                // workgroups at most (one per CU)
     uint32_t bpl;
     uint64_t blocks[2];      // blocks per set, to split the workgroups
 };

@@ -47,9 +47,9 @@ struct BatchParams {
     const DevMsg *msgs;
     const Tile *tiles[2];   // forward-set and inverse-set queues
     uint32_t n_tiles[2];
-    uint32_t *counters;     // dynamic pulls of each queue, then one flag word per workgroup
-    uint32_t n_wg_forward_first;  // workgroups that start on the forward queue
+    uint32_t *counters;     // dynamic pulls of each queue, and the workgroups that finished
     uint32_t n_static[2];   // tiles handed out statically (one per wave of the starting WGs)
+    uint32_t n_wg[2];       // workgroups that start on each queue
     uint32_t pull[2];       // consecutive tiles a wave takes per pull of a queue
     const uint8_t *keys;    // raw key bytes, 32-byte stride (device expansion)
     const uint32_t *sched;  // or resident schedules, kSchedWords per key slot
@@ -749,7 +749,7 @@ __device__ void cbc_encrypt_group(const uint32_t *lds, const Bases &b, const Bat
 template <int WG>
 __global__ __launch_bounds__(WG) void cbc_encrypt_kernel(BatchParams p, const Tile *groups,
                                                          uint32_t n_groups) {
-    __shared__ uint32_t lds[kFwdWords];
+    __shared__ alignas(16) uint32_t lds[kFwdWords];
     stage_tables<false, WG>(lds, p.tables);
     const Bases b = lane_bases();
     // Groups are sorted longest first.  Wave w of workgroup b starts on group
@@ -808,7 +808,8 @@ __device__ __forceinline__ void drain_queue(const uint32_t *lds, const Bases &b,
             // counter, whose atomics would otherwise bound batches of many
             // short tiles.
             uint32_t c = 0;
-            if ((threadIdx.x & 63u) == 0) c = atomicAdd(&p.counters[set], p.pull[set]);
+            if ((threadIdx.x & 63u) == 0)
+                c = atomicAdd(&p.counters[kQueueStride * set], p.pull[set]);
             t = p.n_static[set] + __builtin_amdgcn_readfirstlane(c);
             run_end = t + p.pull[set];
         }
@@ -822,38 +823,48 @@ __device__ __forceinline__ void drain_queue(const uint32_t *lds, const Bases &b,
     }
 }
 
-// One launch for both table sets: workgroups below n_wg_forward_first start
-// on the forward queue, the others on the inverse queue; wave w of the i-th
+// One launch for both table sets: workgroups below n_wg[0] start on the
+// forward queue, the others on the inverse queue; wave w of the i-th
 // workgroup of a set owns static tile 16 i + w of that set.  A workgroup
 // whose queue runs dry waits until all its waves are done with the LDS
 // tables, then stages the other set and helps drain the other queue (if
 // tiles are left there).
 template <int BPL>
 __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
-    __shared__ uint32_t lds[kFwdWords + kInvSWords];
+    __shared__ alignas(16) uint32_t lds[kFwdWords + kInvSWords];
     const Bases b = lane_bases();
-    const uint32_t first = blockIdx.x < p.n_wg_forward_first ? 0u : 1u;
-    const uint32_t wg_in_set = first ? blockIdx.x - p.n_wg_forward_first : blockIdx.x;
+    const uint32_t first = blockIdx.x < p.n_wg[0] ? 0u : 1u;
+    const uint32_t wg_in_set = first ? blockIdx.x - p.n_wg[0] : blockIdx.x;
     const uint32_t my_static = wg_in_set * (kWG / 64) + (threadIdx.x >> 6);
     for (uint32_t pass = 0; pass < 2; ++pass) {
         const uint32_t set = pass ^ first;
         // Stage the set only if this workgroup has work in it: a static tile
-        // (first pass) or dynamic tiles still queued.  One thread decides and
-        // publishes the decision in this workgroup's flag word (the LDS is
-        // full), so that every wave takes the same branch.
-        uint32_t *flag = p.counters + 2 + blockIdx.x;
-        __syncthreads();  // all waves are past the previous queue
-        if (threadIdx.x == 0) {
-            const uint32_t pulled =
-                __hip_atomic_load(&p.counters[set], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bool has_static = pass == 0 && wg_in_set * (kWG / 64) < p.n_tiles[set];
-            const bool has_dynamic = p.n_static[set] < p.n_tiles[set] &&
-                                     pulled < p.n_tiles[set] - p.n_static[set];
-            __hip_atomic_store(flag, (has_static || has_dynamic) ? 1u : 0u, __ATOMIC_RELEASE,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        // (first pass, known to every wave) or dynamic tiles still queued.  For
+        // the latter one thread looks and tells the others through the first
+        // LDS word (the tables there are staged afresh or not needed any more),
+        // so that every wave takes the same branch.  (Told through a word in
+        // device memory with a release and an acquire at agent scope, the
+        // decision cost far more than the staging: each is a write-back or an
+        // invalidation of the XCD's L2, and with 256 workgroups doing both the
+        // table reads that follow missed again and again.  The tables were
+        // staged 33 us after the start of a launch of 256 workgroups and 14 us
+        // after that of 97.)
+        bool work = pass == 0 && wg_in_set * (kWG / 64) < p.n_tiles[set];
+        if (!work) {
+            __syncthreads();  // all waves are past the previous queue
+            if (threadIdx.x == 0) {
+                const uint32_t pulled = __hip_atomic_load(
+                    &p.counters[kQueueStride * set], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lds[0] = p.n_static[set] < p.n_tiles[set] &&
+                                 pulled < p.n_tiles[set] - p.n_static[set]
+                             ? 1u
+                             : 0u;
+            }
+            __syncthreads();
+            work = lds[0] != 0u;
+            __syncthreads();  // every wave has read it before the staging writes there
         }
-        __syncthreads();
-        if (!__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT)) continue;
+        if (!work) continue;
         const uint32_t start = (pass == 0 && my_static < p.n_tiles[set]) ? my_static : kNone;
         // The staging's indices and addresses are recomputed here rather than
         // kept in registers through the whole launch.
@@ -871,16 +882,20 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
     // The last workgroup to finish zeroes the two queue counters (and the
     // exit count), so the next launch on these counters needs no reset
     // kernel before it: every workgroup counts itself out after its last
-    // pull, so no pull of this launch can follow the reset.
+    // pull, so no pull of this launch can follow the reset.  Relaxed atomics
+    // are enough: each pull has returned its value before the barrier, no
+    // other data hangs on the count, and the end of the launch publishes the
+    // zeros.  (An acquire and release add took 5-6 us at the end of a launch.)
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t *exits = p.counters + kExitWord;
-        const uint32_t before = __hip_atomic_fetch_add(exits, 1u, __ATOMIC_ACQ_REL,
+        const uint32_t before = __hip_atomic_fetch_add(exits, 1u, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT);
         if (before == gridDim.x - 1) {
             __hip_atomic_store(&p.counters[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&p.counters[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(exits, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&p.counters[kQueueStride], 0u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -1080,7 +1095,7 @@ __device__ void serve_ring(const uint32_t *lds, const Bases &b, const ResidentLa
 
 template <int BPL>
 __global__ __launch_bounds__(kWG) void resident_kernel(ResidentLaunch p) {
-    __shared__ uint32_t lds[kFwdWords + kInvSWords];
+    __shared__ alignas(16) uint32_t lds[kFwdWords + kInvSWords];
     const Bases b = lane_bases();
     const bool inv = blockIdx.x >= p.n_wg_forward;   // uniform over the workgroup
     if (inv)
@@ -1122,9 +1137,7 @@ int enqueue_t(const BatchLaunch &L, hipStream_t s) {
     if (!total && !L.n_cbc_groups) return AESGPU_OK;
     // About one tile per wave for small batches, one workgroup per CU at most.
     constexpr uint32_t kWaves = kWG / 64;
-    uint32_t grid = (total + kWaves - 1) / kWaves;
-    if (grid > uint32_t(L.n_cu)) grid = uint32_t(L.n_cu);
-    if (grid > 1024) grid = 1024;  // one flag word per workgroup in the counter area
+    uint32_t grid = std::min((total + kWaves - 1) / kWaves, uint32_t(L.n_cu));
     if (grid < 2 && L.n_tiles[0] && L.n_tiles[1]) grid = 2;
     // Split the workgroups between the queues in proportion to their blocks.
     uint32_t fwd = 0;
@@ -1144,7 +1157,7 @@ int enqueue_t(const BatchLaunch &L, hipStream_t s) {
         pull[q] = std::min<uint32_t>(32u, std::max<uint32_t>(1u, dyn / (grid * kWaves * 4u)));
     }
     BatchParams p{L.msgs,     {L.tiles[0], L.tiles[1]}, {L.n_tiles[0], L.n_tiles[1]},
-                  L.counters, fwd,  {n_static[0], n_static[1]}, {pull[0], pull[1]},
+                  L.counters, {n_static[0], n_static[1]}, {fwd, grid - fwd}, {pull[0], pull[1]},
                   L.keys,     L.sched, L.in, L.out, L.tables, L.cbc_list, L.cbc_dummy};
     // Each launch's own status (the thread's last-error state may hold an
     // earlier, unrelated failure).
