@@ -184,7 +184,8 @@ typedef struct {
 #define AESGPU_BATCH_NO_GRAPH 1u /* enqueue the launches directly, no hipGraph */
 
 /* Launch shape of a batch; zero fields take the defaults (4 blocks per lane,
- * 8192-block tiles).  tile_blocks must be a multiple of 64 * blocks_per_lane. */
+ * and tiles of 256 to 8192 blocks, by the size of the batch).  tile_blocks must
+ * be a multiple of 64 * blocks_per_lane. */
 typedef struct {
     uint32_t blocks_per_lane; /* 1, 2 or 4 */
     uint32_t tile_blocks;

@@ -54,6 +54,8 @@ constexpr uint32_t kExitWord = 2 + 1024;
 struct BatchTotals {
     uint64_t total = 0;    // sum of message bytes
     uint64_t blocks[2] = {0, 0};  // blocks per table set
+    uint64_t work[2] = {0, 0};    // rounds of blocks per table set, with the tiles' fixed costs
+    uint64_t head[2] = {0, 0};    // first tiles of each queue, which hold 7/8 of its blocks
     uint64_t in_end = 0;   // max(in_off + n_bytes)
     uint64_t out_end = 0;  // max(out_off + n_bytes)
     uint32_t max_slot = 0;
@@ -79,8 +81,16 @@ struct BatchLaunch {
     uint32_t n_cbc_groups;
     int n_cu;                // workgroups at most (one per CU)
     uint32_t bpl;
-    uint64_t blocks[2];      // blocks per set, to split the workgroups
+    uint64_t blocks[2], work[2], head[2];   // as in BatchTotals
 };
+
+inline void set_totals(BatchLaunch &L, const BatchTotals &t) {
+    for (int q = 0; q < 2; ++q) {
+        L.blocks[q] = t.blocks[q];
+        L.work[q] = t.work[q];
+        L.head[q] = t.head[q];
+    }
+}
 
 // Validates messages and cuts them into tiles of at most tile_blocks blocks,
 // each queue sorted longest first; CBC-encrypt messages form groups (per key

@@ -48,7 +48,7 @@ struct BatchParams {
     const Tile *tiles[2];   // forward-set and inverse-set queues
     uint32_t n_tiles[2];
     uint32_t *counters;     // dynamic pulls of each queue, and the workgroups that finished
-    uint32_t n_static[2];   // tiles handed out statically (one per wave of the starting WGs)
+    uint32_t n_static[2];   // tiles in the workgroups' lists (the first ones of each queue)
     uint32_t n_wg[2];       // workgroups that start on each queue
     uint32_t pull[2];       // consecutive tiles a wave takes per pull of a queue
     const uint8_t *keys;    // raw key bytes, 32-byte stride (device expansion)
@@ -770,12 +770,6 @@ __global__ __launch_bounds__(WG) void cbc_encrypt_kernel(BatchParams p, const Ti
     }
 }
 
-// Runs tiles of one table set's queue until it is empty.  A wave first runs
-// its static tile (`first`, or kNone) and then pulls tiles n_static,
-// n_static + 1, ... from the queue's atomic counter, so a launch does no
-// atomic at all when every tile has a wave of its own.
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-
 // The batch kernel's parameters in its kernel-argument segment (the kernel's
 // only argument, at offset 0), through a pointer the compiler cannot assume
 // constant from one call to the next, so that each call loads afresh.
@@ -786,11 +780,28 @@ __device__ __forceinline__ const BatchParams &kernel_params() {
     return *(const BatchParams *)k;
 }
 
+// LDS words whose high halves a workgroup's waves share while they drain a
+// queue: the count of list rows taken, and whether the queue's dynamic tiles
+// have run out.  They lie behind the forward tables, or in copies of InvS[0],
+// whose entry uses the low half only.
+constexpr uint32_t kRowWord = kFwdWords;
+constexpr uint32_t kDryWord = kFwdWords + 1;
+
+// Runs tiles of one table set's queue until it is empty.  The workgroup's own
+// part of the queue (`own`) is a list: row r of it is one of the r-th n_wg tiles
+// of the queue, taken in alternating order, so that the workgroups' sums come
+// out nearly equal.  Wave w takes row w and then claims the next rows from the
+// count in LDS.  The tiles behind the lists (a large batch's last ones) are
+// pulled from the queue's counter in device memory, which every wave of the
+// chip shares: an atomic there takes its turn at about 77 million a second, so
+// 4096 waves that each find the queue empty once take 53 us.  Batches of a few
+// hundred microseconds therefore have no dynamic tiles at all, and otherwise
+// the first wave that finds none left tells its workgroup.
 template <bool kInv, int BPL>
-__device__ __forceinline__ void drain_queue(const uint32_t *lds, const Bases &b, uint32_t first) {
+__device__ __forceinline__ void drain_queue(uint32_t *lds, const Bases &b, uint32_t wg, bool own) {
     constexpr int set = kInv ? 1 : 0;
-    uint32_t t = first;
-    uint32_t run_end = 0;  // end of the run of tiles taken by the last pull
+    uint32_t row = threadIdx.x >> 6;
+    uint32_t t = 0, run_end = 0;  // the run of tiles taken by the last pull
     KeyCache kc;
     for (;;) {
         // The launch's parameters are read again from the kernel-argument
@@ -800,45 +811,58 @@ __device__ __forceinline__ void drain_queue(const uint32_t *lds, const Bases &b,
         const BatchParams &p = kernel_params();
         const DevMsg *__restrict__ msgs = p.msgs;
         const Tile *__restrict__ tiles = p.tiles[set];
-        t = __builtin_amdgcn_readfirstlane(t);
-        if (t == kNone) {
-            if (p.n_static[set] >= p.n_tiles[set]) break;  // no dynamic tiles at all
-            // One atomic per run of `pull` consecutive tiles (similar in size,
-            // the queue being sorted): all waves of the chip pull from one
-            // counter, whose atomics would otherwise bound batches of many
-            // short tiles.
-            uint32_t c = 0;
-            if ((threadIdx.x & 63u) == 0)
-                c = atomicAdd(&p.counters[kQueueStride * set], p.pull[set]);
-            t = p.n_static[set] + __builtin_amdgcn_readfirstlane(c);
-            run_end = t + p.pull[set];
+        uint32_t at;
+        if (own) {
+            row = __builtin_amdgcn_readfirstlane(row);
+            const uint32_t n = p.n_wg[set];
+            at = row * n + ((row & 1u) ? n - 1u - wg : wg);
+            own = at < p.n_static[set];
         }
-        if (t >= p.n_tiles[set]) break;
+        if (!own) {
+            t = __builtin_amdgcn_readfirstlane(t);
+            if (t >= run_end) {
+                if (p.n_static[set] >= p.n_tiles[set]) break;  // no dynamic tiles at all
+                const uint32_t dry = __hip_atomic_load(lds + kDryWord, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (uniform(dry) >> 16) break;
+                // One atomic per run of `pull` consecutive tiles (similar in
+                // size, the queue being sorted).
+                uint32_t c = 0;
+                if ((threadIdx.x & 63u) == 0)
+                    c = atomicAdd(&p.counters[kQueueStride * set], p.pull[set]);
+                t = p.n_static[set] + __builtin_amdgcn_readfirstlane(c);
+                run_end = t + p.pull[set];
+            }
+            at = t++;
+            if (at >= p.n_tiles[set]) {
+                if ((threadIdx.x & 63u) == 0)
+                    __hip_atomic_fetch_or(lds + kDryWord, 0x10000u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+                break;
+            }
+        }
         // Scalar loads (the index is wave-uniform and nothing writes the
         // descriptors during a launch), so every field is uniform.
-        const Tile tile = load_uniform(tiles + t);
+        const Tile tile = load_uniform(tiles + at);
         const DevMsg m = load_uniform(msgs + tile.msg);
         run_tile<kInv, BPL>(lds, b, p, m, tile, &kc);
-        t = t + 1 < run_end ? t + 1 : kNone;
+        if (own) row = kWG / 64 + claim_share(lds + kRowWord);
     }
 }
 
 // One launch for both table sets: workgroups below n_wg[0] start on the
-// forward queue, the others on the inverse queue; wave w of the i-th
-// workgroup of a set owns static tile 16 i + w of that set.  A workgroup
-// whose queue runs dry waits until all its waves are done with the LDS
-// tables, then stages the other set and helps drain the other queue (if
-// tiles are left there).
+// forward queue, the others on the inverse queue.  A workgroup whose queue runs
+// dry waits until all its waves are done with the LDS tables, then stages the
+// other set and helps drain the other queue (if dynamic tiles are left there).
 template <int BPL>
 __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
     __shared__ alignas(16) uint32_t lds[kFwdWords + kInvSWords];
     const Bases b = lane_bases();
     const uint32_t first = blockIdx.x < p.n_wg[0] ? 0u : 1u;
     const uint32_t wg_in_set = first ? blockIdx.x - p.n_wg[0] : blockIdx.x;
-    const uint32_t my_static = wg_in_set * (kWG / 64) + (threadIdx.x >> 6);
     for (uint32_t pass = 0; pass < 2; ++pass) {
         const uint32_t set = pass ^ first;
-        // Stage the set only if this workgroup has work in it: a static tile
+        // Stage the set only if this workgroup has work in it: a list of its own
         // (first pass, known to every wave) or dynamic tiles still queued.  For
         // the latter one thread looks and tells the others through the first
         // LDS word (the tables there are staged afresh or not needed any more),
@@ -849,12 +873,13 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
         // table reads that follow missed again and again.  The tables were
         // staged 33 us after the start of a launch of 256 workgroups and 14 us
         // after that of 97.)
-        bool work = pass == 0 && wg_in_set * (kWG / 64) < p.n_tiles[set];
+        const bool own = pass == 0 && wg_in_set < p.n_static[set];
+        bool work = own;
         if (!work) {
             __syncthreads();  // all waves are past the previous queue
             if (threadIdx.x == 0) {
-                const uint32_t pulled = __hip_atomic_load(
-                    &p.counters[kQueueStride * set], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t pulled = __hip_atomic_load(&p.counters[kQueueStride * set], __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
                 lds[0] = p.n_static[set] < p.n_tiles[set] &&
                                  pulled < p.n_tiles[set] - p.n_static[set]
                              ? 1u
@@ -865,18 +890,18 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
             __syncthreads();  // every wave has read it before the staging writes there
         }
         if (!work) continue;
-        const uint32_t start = (pass == 0 && my_static < p.n_tiles[set]) ? my_static : kNone;
         // The staging's indices and addresses are recomputed here rather than
         // kept in registers through the whole launch.
         const uint32_t *tables = p.tables;
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+s"(tables), "+v"(tid));
         if (set == 0) {
+            if (tid < 2) lds[kRowWord + tid] = 0u;   // published by the staging's barrier
             stage_tables_tid<false>(lds, tables, tid);
-            drain_queue<false, BPL>(lds, b, start);
+            drain_queue<false, BPL>(lds, b, wg_in_set, own);
         } else {
             stage_tables_tid<true>(lds, tables, tid);
-            drain_queue<true, BPL>(lds, b, start);
+            drain_queue<true, BPL>(lds, b, wg_in_set, own);
         }
     }
     // The last workgroup to finish zeroes the two queue counters (and the
@@ -893,8 +918,7 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
                                                        __HIP_MEMORY_SCOPE_AGENT);
         if (before == gridDim.x - 1) {
             __hip_atomic_store(&p.counters[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&p.counters[kQueueStride], 0u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&p.counters[kQueueStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -1131,33 +1155,45 @@ __global__ __launch_bounds__(kWG) void resident_kernel(ResidentLaunch p) {
     }
 }
 
+// Rows of a workgroup's list: they and the 16 last claims fit its 16-bit count.
+constexpr uint64_t kMaxRows = 60000;
+constexpr uint64_t kListBlocks = 65536;
+
 template <int BPL>
 int enqueue_t(const BatchLaunch &L, hipStream_t s) {
     const uint32_t total = L.n_tiles[0] + L.n_tiles[1];
     if (!total && !L.n_cbc_groups) return AESGPU_OK;
-    // About one tile per wave for small batches, one workgroup per CU at most.
+    // One workgroup per CU, fewer if there are fewer tiles.
     constexpr uint32_t kWaves = kWG / 64;
-    uint32_t grid = std::min((total + kWaves - 1) / kWaves, uint32_t(L.n_cu));
+    uint32_t grid = std::min(total, uint32_t(L.n_cu));
     if (grid < 2 && L.n_tiles[0] && L.n_tiles[1]) grid = 2;
-    // Split the workgroups between the queues in proportion to their blocks.
+    // Split the workgroups between the queues in proportion to their work.
     uint32_t fwd = 0;
     if (!L.n_tiles[1]) {
         fwd = grid;
     } else if (L.n_tiles[0]) {
-        const double share = double(L.blocks[0]) / double(L.blocks[0] + L.blocks[1]);
+        const double share = double(L.work[0]) / double(L.work[0] + L.work[1]);
         fwd = uint32_t(share * grid + 0.5);
         fwd = fwd < 1 ? 1 : (fwd > grid - 1 ? grid - 1 : fwd);
     }
-    // Dynamic tiles per pull: about four pulls per wave of the grid for each
-    // queue, at most 32 tiles.
-    uint32_t pull[2] = {1u, 1u};
-    const uint32_t n_static[2] = {fwd * kWaves, (grid - fwd) * kWaves};
-    for (int q = 0; q < 2 && grid; ++q) {  // grid is 0 when only CBC encryption runs
-        const uint32_t dyn = L.n_tiles[q] > n_static[q] ? L.n_tiles[q] - n_static[q] : 0u;
+    // Tiles in the workgroups' lists: all of them in batches that keep a CU busy
+    // for less than about kListBlocks blocks; in larger ones those that hold the
+    // first seven eighths of the blocks, and the rest are pulled as waves get free,
+    // about four pulls per wave of the grid, at most 32 tiles each.
+    const uint32_t n_wg[2] = {fwd, grid - fwd};
+    uint32_t n_static[2] = {0, 0}, pull[2] = {1u, 1u};
+    for (int q = 0; q < 2; ++q) {
+        if (!n_wg[q]) continue;
+        const uint64_t rows = (uint64_t(L.n_tiles[q]) + n_wg[q] - 1) / n_wg[q];
+        uint64_t listed = rows;
+        if (L.blocks[q] / n_wg[q] > kListBlocks) listed = std::max<uint64_t>(L.head[q] / n_wg[q], kWaves);
+        listed = std::min<uint64_t>(listed, kMaxRows);
+        n_static[q] = uint32_t(std::min<uint64_t>(listed * n_wg[q], L.n_tiles[q]));
+        const uint32_t dyn = L.n_tiles[q] - n_static[q];
         pull[q] = std::min<uint32_t>(32u, std::max<uint32_t>(1u, dyn / (grid * kWaves * 4u)));
     }
     BatchParams p{L.msgs,     {L.tiles[0], L.tiles[1]}, {L.n_tiles[0], L.n_tiles[1]},
-                  L.counters, {n_static[0], n_static[1]}, {fwd, grid - fwd}, {pull[0], pull[1]},
+                  L.counters, {n_static[0], n_static[1]}, {n_wg[0], n_wg[1]}, {pull[0], pull[1]},
                   L.keys,     L.sched, L.in, L.out, L.tables, L.cbc_list, L.cbc_dummy};
     // Each launch's own status (the thread's last-error state may hold an
     // earlier, unrelated failure).
@@ -1270,12 +1306,21 @@ int build_tiles(const aesgpu_msg *msgs, size_t m, uint32_t tile_blocks, std::vec
         for (uint64_t f = 0; f < n_blocks;) {
             const uint64_t n = std::min<uint64_t>(f ? tile_blocks : first_len, n_blocks - f);
             tiles[set].push_back(Tile{uint32_t(i), uint32_t(n), f});
+            // A tile's rounds run on groups of 64 blocks; its key expansion
+            // and set-up cost about as much as 24 blocks more.
+            tot.work[set] += uint64_t(d.nr) * ((n + 63) / 64 * 64 + 24);
             f += n;
         }
     }
     for (auto &t : tiles)
         std::stable_sort(t.begin(), t.end(),
                          [](const Tile &a, const Tile &b) { return a.n_blocks > b.n_blocks; });
+    for (int q = 0; q < 2; ++q) {
+        uint64_t left = tot.blocks[q] / 8;
+        size_t i = tiles[q].size();
+        while (i > 0 && tiles[q][i - 1].n_blocks <= left) left -= tiles[q][--i].n_blocks;
+        tot.head[q] = i;
+    }
     // CBC-encrypt groups: per key size, longest first, 16 messages (four
     // lanes each) per group; all groups longest first, since each runs its blocks one
     // after another.
@@ -1301,6 +1346,25 @@ using namespace aesgpu;
 namespace {
 constexpr uint32_t kDefaultBpl = 4;
 constexpr uint32_t kDefaultTileBlocks = 8192;
+
+// Blocks per tile where the caller leaves it to the library: about two tiles
+// for every wave of the chip, 256 to kDefaultTileBlocks blocks.  A wave needs
+// tens of microseconds for some thousand blocks, so with one size for all the
+// time of a small batch was that of its longest tile; tiles below 256 blocks
+// give up the whole steps and pay a key expansion for little work.  Measured
+// with lists and no graph, us at 256 / 512 / 1024 / 2048 / 8192 blocks per tile:
+// 256 messages, 23 MB 33 / 34 / 41 / 64 / 211; 1,146 messages, 83 MB
+// 82 / 79 / 78 / 92 / 220; 4,096 messages, 111 MB 106 / 98 / 96 / 102 / 218;
+// 7,459 messages, 640 MB decrypted 702 / 606 / 570 / 575 / 593.
+constexpr uint64_t kTilesPerWave = 2;
+uint32_t default_tile_blocks(const aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m) {
+    uint64_t blocks = 0;
+    for (size_t i = 0; i < m && blocks < (uint64_t(1) << 40); ++i)
+        blocks += std::min<uint64_t>(msgs[i].n_bytes, uint64_t(1) << 50) / 16;
+    const uint64_t waves = uint64_t(ctx->n_cu) * (kWG / 64);
+    const uint64_t t = (blocks / (waves * kTilesPerWave) + 255) / 256 * 256;
+    return uint32_t(std::min<uint64_t>(std::max<uint64_t>(t, 256), kDefaultTileBlocks));
+}
 }  // namespace
 
 // Descriptor scratch of aesgpu_batch_run_noalloc(): one copy on each GPU the
@@ -1373,15 +1437,16 @@ int check_run(const BatchTotals &tot, const uint8_t *d_keys, size_t n_key_slots,
     return AESGPU_OK;
 }
 
-// The launch shape a config asks for (NULL: the defaults).
+// The launch shape a config asks for (NULL: the defaults; tile_blocks 0: the
+// library's choice).
 int batch_shape(const aesgpu_batch_config *cfg, uint32_t &bpl, uint32_t &tile_blocks,
                 bool &use_graph) {
     bpl = kDefaultBpl;
-    tile_blocks = kDefaultTileBlocks;
+    tile_blocks = 0;
     use_graph = true;
     if (cfg) {
         if (cfg->blocks_per_lane) bpl = cfg->blocks_per_lane;
-        if (cfg->tile_blocks) tile_blocks = cfg->tile_blocks;
+        tile_blocks = cfg->tile_blocks;
         use_graph = !(cfg->flags & AESGPU_BATCH_NO_GRAPH);
     }
     if (bpl != 1 && bpl != 2 && bpl != 4) return AESGPU_EINVAL;
@@ -1415,8 +1480,7 @@ int enqueue(aesgpu_batch *b, const uint8_t *keys, const void *in, void *out, hip
     L.n_cbc_groups = uint32_t(b->n_cbc_groups);
     L.n_cu = b->ctx->n_cu;
     L.bpl = b->bpl;
-    L.blocks[0] = b->tot.blocks[0];
-    L.blocks[1] = b->tot.blocks[1];
+    set_totals(L, b->tot);
     return enqueue_batch(L, s);
 }
 
@@ -1434,6 +1498,7 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     bool use_graph;
     const int shape = batch_shape(cfg, bpl, tile_blocks, use_graph);
     if (shape != AESGPU_OK) return shape;
+    if (!tile_blocks) tile_blocks = default_tile_blocks(ctx, msgs, m);
 
     std::vector<DevMsg> dm;
     std::vector<Tile> tiles[2];
@@ -1580,7 +1645,9 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     thread_local std::vector<Tile> cbc_groups;
     thread_local std::vector<uint8_t> staging;
     BatchTotals tot;
-    const int st = build_tiles(msgs, m, tile_blocks, dm, tiles, cbc_list, cbc_groups, tot);
+    const bool choose = tile_blocks == 0;
+    if (choose) tile_blocks = default_tile_blocks(ctx, msgs, m);
+    int st = build_tiles(msgs, m, tile_blocks, dm, tiles, cbc_list, cbc_groups, tot);
     if (st != AESGPU_OK) return st;
     if (tiles[0].size() + tiles[1].size() + cbc_groups.size() == 0) return AESGPU_OK;
     const int chk = check_run(tot, d_keys, n_key_slots, d_in, in_bytes, d_out, out_bytes);
@@ -1588,14 +1655,22 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     // Scratch layout, each part 256-byte aligned: queue counters (zero, as the
     // batch kernel expects before a launch), messages, forward tiles, inverse
     // tiles, CBC-encryption groups, 16 dummy bytes, CBC list.
-    const size_t o_msgs = align256(kCounterBytes);
-    const size_t o_t0 = o_msgs + align256(m * sizeof(DevMsg));
-    const size_t o_t1 = o_t0 + align256(tiles[0].size() * sizeof(Tile));
-    const size_t o_cg = o_t1 + align256(tiles[1].size() * sizeof(Tile));
-    const size_t o_dummy = o_cg + align256(cbc_groups.size() * sizeof(Tile));
-    const size_t o_cl = o_dummy + 256;
-    const size_t total = o_cl + cbc_list.size() * sizeof(uint32_t);
-    if (total > AESGPU_NOALLOC_SCRATCH_BYTES) return AESGPU_ESCRATCH;
+    size_t o_msgs, o_t0, o_t1, o_cg, o_dummy, o_cl, total;
+    for (;;) {
+        o_msgs = align256(kCounterBytes);
+        o_t0 = o_msgs + align256(m * sizeof(DevMsg));
+        o_t1 = o_t0 + align256(tiles[0].size() * sizeof(Tile));
+        o_cg = o_t1 + align256(tiles[1].size() * sizeof(Tile));
+        o_dummy = o_cg + align256(cbc_groups.size() * sizeof(Tile));
+        o_cl = o_dummy + 256;
+        total = o_cl + cbc_list.size() * sizeof(uint32_t);
+        if (total <= AESGPU_NOALLOC_SCRATCH_BYTES) break;
+        // The library's own small tiles must not cost a batch its place.
+        if (!choose || tile_blocks == kDefaultTileBlocks) return AESGPU_ESCRATCH;
+        tile_blocks = kDefaultTileBlocks;
+        st = build_tiles(msgs, m, tile_blocks, dm, tiles, cbc_list, cbc_groups, tot);
+        if (st != AESGPU_OK) return st;
+    }
     // The queue counters must start at zero; the padding between parts is
     // never read.
     staging.resize(total);
@@ -1635,8 +1710,7 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     L.n_cbc_groups = uint32_t(cbc_groups.size());
     L.n_cu = ctx->n_cu;
     L.bpl = bpl;
-    L.blocks[0] = tot.blocks[0];
-    L.blocks[1] = tot.blocks[1];
+    set_totals(L, tot);
     (void)use_graph;
     return enqueue_batch(L, s);
 }

@@ -169,6 +169,30 @@ __device__ __forceinline__ void stage_tables(uint32_t *lds, const uint32_t *__re
     stage_tables_tid<kInv, WG, kGroup>(lds, g, threadIdx.x);
 }
 
+// The next share (or tile) for this wave: lane 0 adds one to the workgroup's count in
+// LDS and the old count goes to every lane.  The exec mask is narrowed inside
+// the asm block, which also waits for the result, so the tile loop has no
+// branch.  The count is kept in the high half of its word (with the inverse
+// tables the low half holds an InvS table entry, which the add leaves as it
+// is).  Needs all 64 lanes of the wave active.  No memory clobber: the only
+// LDS data the add shares a word with is read-only, and with the clobber the
+// compiler kept only about five table reads in flight in AES-256 encryption.
+__device__ __forceinline__ uint32_t claim_share(uint32_t *count) {
+    uint32_t old = 0;
+    uint64_t exec_save;
+    const uint32_t addr = uint32_t(reinterpret_cast<uintptr_t>(count));   // LDS offset
+    asm volatile(
+        "s_mov_b64 %1, exec\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "ds_add_rtn_u32 %0, %2, %3\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "s_mov_b64 exec, %1\n\t"
+        "s_nop 4"
+        : "+v"(old), "=&s"(exec_save)
+        : "v"(addr), "v"(0x10000u));
+    return uint32_t(__builtin_amdgcn_readfirstlane(old)) >> 16;
+}
+
 __device__ __forceinline__ uint32_t bswap32(uint32_t v) {
     return __builtin_amdgcn_perm(v, v, 0x00010203u);
 }

@@ -123,30 +123,6 @@ __device__ __forceinline__ void store_block(const TileView &t, int j, const uint
     buffer_store16(t.out, lane_offset<kWaveMajor, BPL>(t, j), o);
 }
 
-// The next share for this wave: lane 0 adds one to the workgroup's count in
-// LDS and the old count goes to every lane.  The exec mask is narrowed inside
-// the asm block, which also waits for the result, so the tile loop has no
-// branch.  The count is kept in the high half of its word (in decryption
-// kernels the low half holds an InvS table entry, which the add leaves as it
-// is).  Needs all 64 lanes of the wave active.  No memory clobber: the only
-// LDS data the add shares a word with is read-only, and with the clobber the
-// compiler kept only about five table reads in flight in AES-256 encryption.
-__device__ __forceinline__ uint32_t claim_share(uint32_t *count) {
-    uint32_t old = 0;
-    uint64_t exec_save;
-    const uint32_t addr = uint32_t(reinterpret_cast<uintptr_t>(count));   // LDS offset
-    asm volatile(
-        "s_mov_b64 %1, exec\n\t"
-        "s_mov_b64 exec, 1\n\t"
-        "ds_add_rtn_u32 %0, %2, %3\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "s_mov_b64 exec, %1\n\t"
-        "s_nop 4"
-        : "+v"(old), "=&s"(exec_save)
-        : "v"(addr), "v"(0x10000u));
-    return uint32_t(__builtin_amdgcn_readfirstlane(old)) >> 16;
-}
-
 // Lane L gets x of lane L - 1 (a DPP shift of the wave); lane 0 keeps lane0.
 __device__ __forceinline__ uint4 from_lane_below(const uint4 &lane0, const uint4 &x) {
     return make_uint4(__builtin_amdgcn_update_dpp(lane0.x, x.x, 0x138, 0xf, 0xf, false),

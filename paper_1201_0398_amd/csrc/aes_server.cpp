@@ -363,8 +363,7 @@ int launch_slot(aesgpu_server *s, Slot &slot, bool backlog) {
     L.n_cbc_groups = 0;
     L.n_cu = s->ctx->n_cu;
     L.bpl = s->cfg.blocks_per_lane;
-    L.blocks[0] = tot.blocks[0];
-    L.blocks[1] = tot.blocks[1];
+    set_totals(L, tot);
     st = enqueue_batch(L, slot.stream);
     if (st != AESGPU_OK) return st;
     return hipEventRecord(slot.done, slot.stream) == hipSuccess ? AESGPU_OK : AESGPU_EHIP;
