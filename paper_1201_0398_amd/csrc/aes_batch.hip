@@ -637,19 +637,33 @@ __device__ __forceinline__ uint32_t quad_rot(uint32_t v) {
 }
 
 // One round of Eq. (1) on a block held by four lanes, lane q holding state
-// word q: output word q reads byte k of word q + k (mod 4), which the quad
-// permutations bring to lane q.  The last round takes the S-box bytes from
-// the T tables as last_round_fwd does.
+// word q: output word q reads byte k of word q + k (mod 4).  Each lane looks up
+// the four bytes of its own word, and the quad permutations bring the table
+// words to the lanes whose outputs they belong to, as operands of the XORs (a
+// DPP XOR each).  What bounds a group is this chain of dependent steps, round
+// after round, so what counts is its length: with the permutations before the
+// lookups, as moves of the state words, it had three more steps and the
+// wait between a write and a DPP read of it.  The last round takes the
+// S-box bytes from the T tables as last_round_fwd does.
 template <bool kLast>
 __device__ __forceinline__ uint32_t quad_round(const uint32_t *lds, const Bases &b, uint32_t s,
                                                uint32_t k) {
-    const uint32_t s1 = quad_rot<1>(s), s2 = quad_rot<2>(s), s3 = quad_rot<3>(s);
-    if constexpr (kLast)
-        return merge4_xor(tlook<0>(lds, s, b.t[2]), tlook<1>(lds, s1, b.t[3]),
-                          tlook<2>(lds, s2, b.t[0]), tlook<3>(lds, s3, b.t[1]), k);
-    return xor3(xor3(tlook<0>(lds, s, b.t[0]), tlook<1>(lds, s1, b.t[1]),
-                     tlook<2>(lds, s2, b.t[2])),
-                tlook<3>(lds, s3, b.t[3]), k);
+    uint32_t t0, t1, t2, t3;
+    if constexpr (kLast) {
+        t0 = tlook<0>(lds, s, b.t[2]) & 0xFFu;
+        t1 = tlook<1>(lds, s, b.t[3]) & 0xFF00u;
+        t2 = tlook<2>(lds, s, b.t[0]) & 0xFF0000u;
+        t3 = tlook<3>(lds, s, b.t[1]) & 0xFF000000u;
+    } else {
+        t0 = tlook<0>(lds, s, b.t[0]);
+        t1 = tlook<1>(lds, s, b.t[1]);
+        t2 = tlook<2>(lds, s, b.t[2]);
+        t3 = tlook<3>(lds, s, b.t[3]);
+    }
+    uint32_t o = t0 ^ k;
+    o ^= quad_rot<1>(t1);
+    o ^= quad_rot<2>(t2);
+    return o ^ quad_rot<3>(t3);
 }
 
 // FIPS-197 KeyExpansion of the quad's key; lane q keeps column q of every
