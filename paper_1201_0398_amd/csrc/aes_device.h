@@ -125,48 +125,45 @@ __device__ __forceinline__ void last_round_inv(const uint32_t *lds, const Bases 
 }
 
 // Copies the table set into the LDS image; tid is the thread's index in the
-// workgroup.  Loads are issued in groups of kGroup before their LDS writes, so
-// the staging costs a few L2 round trips instead of one per word; a wave's
-// loads hit two distinct words (every lane of a wave writes copies of the same
-// table entry).  Needs blockDim.x == WG.
-template <bool kInv, int WG = kWG, int kGroup = 16>
+// workgroup.  Needs blockDim.x == WG.  Each table word is loaded once per
+// workgroup and its thread writes all 32 copies, four to a ds_write_b128: at
+// step i the lane takes copies 4 * ((i + tid) % 8) .. + 3, so eight
+// neighbouring lanes (neighbouring entries, 256 bytes apart) cover all the
+// banks and the writes run at the LDS's 128 bytes per clock.  What bounds it
+// is then that rate: 128 KiB are 1024 clocks.
+template <bool kInv, int WG = kWG>
 __device__ __forceinline__ void stage_tables_tid(uint32_t *lds, const uint32_t *__restrict__ g,
                                                  uint32_t tid) {
-    static_assert(kFwdWords % (WG * kGroup) == 0 && kInvSWords % WG == 0, "workgroup size");
+    static_assert(1024 % WG == 0 && WG % 256 == 0, "workgroup size");
     const uint32_t *src = g + (kInv ? kTd : kTe);
-    constexpr int kPer = kFwdWords / WG;
-#pragma unroll 1
-    for (int k0 = 0; k0 < kPer; k0 += kGroup) {
-        uint32_t v[kGroup];
+    constexpr int kPer = 1024 / WG;
+    uint32_t v[kPer], w = 0;
 #pragma unroll
-        for (int k = 0; k < kGroup; ++k) {
-            const uint32_t i = tid + uint32_t(k0 + k) * WG;
-            const uint32_t t = ((i >> 14) << 1) | ((i >> 5) & 1u);
-            const uint32_t x = (i >> 6) & 0xFFu;
-            v[k] = src[t * 256u + x];
-        }
+    for (int k = 0; k < kPer; ++k) v[k] = src[tid + uint32_t(k) * WG];
+    if constexpr (kInv) w = g[kInvSS + (tid & 255u)];
 #pragma unroll
-        for (int k = 0; k < kGroup; ++k) lds[tid + uint32_t(k0 + k) * WG] = v[k];
+    for (int k = 0; k < kPer; ++k) {
+        const uint32_t e = tid + uint32_t(k) * WG, t = e >> 8, x = e & 255u;
+        uint32_t *row = lds + (t >> 1) * 16384u + x * 64u + (t & 1u) * 32u;
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            *reinterpret_cast<uint4 *>(row + 4u * ((i + tid) & 7u)) = make_uint4(v[k], v[k], v[k], v[k]);
     }
     if constexpr (kInv) {
-        constexpr int kPerS = kInvSWords / WG;
-#pragma unroll 1
-        for (int k0 = 0; k0 < kPerS; k0 += 8) {
-            uint32_t w[8];
+        // The inverse S-box words: WG / 256 threads share an entry's copies.
+        constexpr uint32_t kEach = 8 / (WG / 256);
+        uint32_t *row = lds + kFwdWords + (tid & 255u) * 32u;
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                w[k] = k0 + k < kPerS ? g[kInvSS + ((tid + uint32_t(k0 + k) * WG) >> 5)] : 0u;
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (k0 + k < kPerS) lds[kFwdWords + tid + uint32_t(k0 + k) * WG] = w[k];
-        }
+        for (uint32_t i = 0; i < kEach; ++i)
+            *reinterpret_cast<uint4 *>(row + 4u * (((tid >> 8) * kEach + i + tid) & 7u)) =
+                make_uint4(w, w, w, w);
     }
     __syncthreads();
 }
 
-template <bool kInv, int WG = kWG, int kGroup = 16>
+template <bool kInv, int WG = kWG>
 __device__ __forceinline__ void stage_tables(uint32_t *lds, const uint32_t *__restrict__ g) {
-    stage_tables_tid<kInv, WG, kGroup>(lds, g, threadIdx.x);
+    stage_tables_tid<kInv, WG>(lds, g, threadIdx.x);
 }
 
 // The next share (or tile) for this wave: lane 0 adds one to the workgroup's count in
