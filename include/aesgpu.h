@@ -187,7 +187,7 @@ typedef struct {
  * and tiles of 256 to 8192 blocks, by the size of the batch).  tile_blocks must
  * be a multiple of 64 * blocks_per_lane. */
 typedef struct {
-    uint32_t blocks_per_lane; /* 1, 2 or 4 */
+    uint32_t blocks_per_lane; /* 1, 2 or 4 (decryption tiles run at 2 where it is 4) */
     uint32_t tile_blocks;
     uint32_t flags;           /* AESGPU_BATCH_* */
 } aesgpu_batch_config;

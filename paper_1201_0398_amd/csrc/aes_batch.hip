@@ -11,17 +11,19 @@
 //   key size, four lanes per message (one state column each), run by a
 //   launch of their own (its round keys live in registers, which the
 //   block-parallel kernel cannot spare).
-// * Device: each workgroup (1024 threads, one per CU) stages its table set in
-//   LDS once.  Each wave then pulls tile numbers from an atomic counter until
-//   the queue is empty (every wave reaches that exit; no wave waits on
-//   another).  For each tile the wave expands the message key (FIPS-197
-//   KeyExpansion, the key schedule the paper's section 2.1 defers to) with
-//   wave-uniform table reads into one register, word i in lane i;
-//   decryption keys get InvMixColumns lane-parallel.  The rounds are the
-//   single-buffer kernel's (Eq. (1)); in whole steps the middle rounds run
-//   as one straight sequence shared by the three key sizes, their round keys
-//   given to every lane by DPP row broadcasts.  CTR tiles precompute their
-//   round-1 constants.
+// * Device: each workgroup (1024 threads, one per CU) has a list of one queue's
+//   tiles and stages that queue's table set in LDS once.  Its waves claim the
+//   list's tiles from a count in LDS; the last tiles of a large batch are pulled
+//   from an atomic counter by whoever is free (every wave reaches the end of
+//   both; no wave waits on another).  For each tile the wave expands the
+//   message key (FIPS-197 KeyExpansion, the key schedule the paper's section 2.1
+//   defers to) into one register, word i in lane i; decryption keys get
+//   InvMixColumns lane-parallel.  While it does, the tile's first blocks are on
+//   their way, and while the tile runs, so are the next one's descriptors and
+//   key.  The rounds are the single-buffer kernel's (Eq. (1)); in whole steps
+//   the middle rounds run as one straight sequence shared by the three key
+//   sizes, their round keys given to every lane by DPP row broadcasts.  CTR
+//   tiles precompute their round-1 constants.
 // * The persistent launches are captured once into a hipGraph and replayed
 //   (the kernel leaves its queue counters at zero); the graph is re-captured
 //   when the buffers change.
@@ -60,60 +62,101 @@ struct BatchParams {
     uint4 *cbc_dummy;          // 16 bytes nobody reads (stores with nothing to store)
 };
 
+// The lane's index, as a value the compiler cannot tell is the same each time:
+// otherwise everything worked out from it (offsets, comparisons) is kept in
+// registers through the whole launch.
+__device__ __forceinline__ uint32_t fresh_lane() {
+    uint32_t lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 // Wave-uniform reads of copy 0 of a table (every lane reads the same word, so
 // the LDS broadcasts it and the compiler moves the result to an SGPR).
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-template <bool kInv>
-__device__ __forceinline__ uint32_t sbox_u(const uint32_t *lds, uint32_t x) {
-    // Forward set: S(x) is byte 1 of T0[x]; inverse set: byte 1 of the S word.
-    const uint32_t w = kInv ? lds_at(lds, kInvSByte + (x << 7)) : lds_at(lds, x << 8);
-    return (uniform(w) >> 8) & 0xFFu;
-}
-
-template <bool kInv>
-__device__ __forceinline__ uint32_t sub_word_u(const uint32_t *lds, uint32_t w) {
-    return sbox_u<kInv>(lds, w & 0xFFu) | (sbox_u<kInv>(lds, (w >> 8) & 0xFFu) << 8) |
-           (sbox_u<kInv>(lds, (w >> 16) & 0xFFu) << 16) | (sbox_u<kInv>(lds, w >> 24) << 24);
-}
 
 // T_t[x] (or Td_t[x]) from copy 0.
 __device__ __forceinline__ uint32_t table_u(const uint32_t *lds, int t, uint32_t x) {
     return uniform(lds_at(lds, uint32_t(t >> 1) * 65536u + (x << 8) + uint32_t(t & 1) * 128u));
 }
 
-// FIPS-197 KeyExpansion.  Word i of the schedule (little-endian) is computed
-// in SGPRs and stored in lane i of the returned VGPR, so a whole schedule
-// occupies one register; only the last nk words stay live in SGPRs for the
-// recurrence.
+// SubWord(w) with the word rotated by ROT bytes first, in two halves whose XOR
+// it is (their bytes are disjoint).  Forward set: the S-box byte lies in byte 0
+// of T2, 1 of T3, 2 of T0 and 3 of T1; inverse set: in byte 1 of the S words.
+template <bool kInv, int ROT>
+__device__ __forceinline__ void sub_word(const uint32_t *lds, const Bases &b, uint32_t w,
+                                         uint32_t &lo, uint32_t &hi) {
+    if constexpr (kInv) {
+        const uint32_t v0 = islook<ROT>(lds, w, b.invs), v1 = islook<(1 + ROT) & 3>(lds, w, b.invs),
+                       v2 = islook<(2 + ROT) & 3>(lds, w, b.invs),
+                       v3 = islook<(3 + ROT) & 3>(lds, w, b.invs);
+        lo = __builtin_amdgcn_perm(v1, v0, 0x0C0C0501u);
+        hi = __builtin_amdgcn_perm(v3, v2, 0x05010C0Cu);
+    } else {
+        const uint32_t v0 = tlook<ROT>(lds, w, b.t[2]), v1 = tlook<(1 + ROT) & 3>(lds, w, b.t[3]),
+                       v2 = tlook<(2 + ROT) & 3>(lds, w, b.t[0]),
+                       v3 = tlook<(3 + ROT) & 3>(lds, w, b.t[1]);
+        lo = __builtin_amdgcn_perm(v1, v0, 0x0C0C0500u);
+        hi = __builtin_amdgcn_perm(v3, v2, 0x07020C0Cu);
+    }
+}
+
+// Lane 4r + c takes word 4r + c of the schedule.
+template <int R, int N>
+__device__ __forceinline__ void keep_round(const uint32_t (&w)[N], uint32_t lane, uint32_t &kreg) {
+    const uint32_t w0 = w[4 * R], w1 = w[4 * R + 1], w2 = w[4 * R + 2], w3 = w[4 * R + 3];
+    const uint32_t col = lane & 3u;
+    uint32_t v = col == 1u ? w1 : w0;
+    v = col == 2u ? w2 : v;
+    v = col == 3u ? w3 : v;
+    kreg = (lane >> 2) == uint32_t(R) ? v : kreg;
+}
+
+// Words I .. of a schedule whose earlier words are in w: each S-box lookup gives
+// the next nk words (AES-256: four), namely its XOR with the running XOR of the
+// words nk before them.  Rounds R .. are not in kreg yet.
+template <bool kInv, int NR, int I, uint32_t kRcon, int R>
+__device__ __forceinline__ void expand_words(const uint32_t *lds, const Bases &b, uint32_t lane,
+                                             uint32_t (&w)[4 * (NR + 1)], uint32_t &kreg) {
+    constexpr int nk = NR - 6, nw = 4 * (NR + 1), kEach = nk == 8 ? 4 : nk;
+    if constexpr (R <= NR && 4 * R + 4 <= I) {
+        keep_round<R>(w, lane, kreg);
+        expand_words<kInv, NR, I, kRcon, R + 1>(lds, b, lane, w, kreg);
+    } else if constexpr (I < nw) {
+        constexpr bool kRot = !(nk == 8 && I % 8 == 4);
+        uint32_t lo, hi;
+        // RotWord is a right rotation of the little-endian word.
+        sub_word<kInv, kRot ? 1 : 0>(lds, b, w[I - 1], lo, hi);
+        uint32_t run = kRot ? kRcon : 0u;
+#pragma unroll
+        for (int k = 0; k < (I + kEach <= nw ? kEach : nw - I); ++k) {
+            run ^= w[I + k - nk];
+            asm volatile("" : "+v"(run));   // made before the lookup is back
+            w[I + k] = xor3(lo, hi, run);
+        }
+        // x * rcon in GF(2^8)
+        constexpr uint32_t kNext = kRot ? ((kRcon << 1) ^ ((kRcon >> 7) * 0x1Bu)) & 0xFFu : kRcon;
+        expand_words<kInv, NR, (I + kEach < nw ? I + kEach : nw), kNext, R>(lds, b, lane, w, kreg);
+    }
+}
+
+// FIPS-197 KeyExpansion of the key whose word i lane i holds (i < 8).  Every
+// lane computes every word, from its own table copies; word i of the schedule
+// (little-endian) ends up in lane i of the returned VGPR.  A wave spends the
+// expansion waiting for ten to thirteen S-box lookups one after the other, so
+// the rest is kept off that chain: the XORs of the old words are made beforehand
+// and each new word is one XOR of three away from the lookup.  (In SGPRs, with a
+// move to the scalar unit and a dozen scalar instructions in each step, it took
+// about 2 us.)
 template <bool kInv, int NR>
-__device__ __forceinline__ uint32_t expand_key(const uint32_t *lds, const uint32_t *key) {
+__device__ __forceinline__ uint32_t expand_key(const uint32_t *lds, const Bases &b, uint32_t key) {
     constexpr int nk = NR - 6;
-    // The lane index is re-read here: otherwise the compiler keeps the 60
-    // lane comparisons below as masks through the whole launch.
-    uint32_t lane = threadIdx.x & 63u;
-    asm volatile("" : "+v"(lane));
-    uint32_t win[8];  // win[i % nk] = word i
+    const uint32_t lane = fresh_lane();
+    uint32_t w[4 * (NR + 1)];
     uint32_t kreg = 0;
 #pragma unroll
-    for (int i = 0; i < nk; ++i) {
-        win[i] = uniform(key[i]);
-        kreg = lane == uint32_t(i) ? win[i] : kreg;
-    }
-    uint32_t rcon = 1;
-#pragma unroll
-    for (int i = nk; i < 4 * (NR + 1); ++i) {
-        uint32_t t = win[(i - 1) % nk];
-        if (i % nk == 0) {
-            // RotWord is a right rotation of the little-endian word.
-            t = sub_word_u<kInv>(lds, (t >> 8) | (t << 24)) ^ rcon;
-            rcon = ((rcon << 1) ^ ((rcon >> 7) * 0x1Bu)) & 0xFFu;  // x * rcon in GF(2^8)
-        } else if (nk == 8 && i % nk == 4) {
-            t = sub_word_u<kInv>(lds, t);
-        }
-        win[i % nk] = uniform(win[i % nk] ^ t);
-        kreg = lane == uint32_t(i) ? win[i % nk] : kreg;
-    }
+    for (int i = 0; i < nk; ++i) w[i] = __builtin_amdgcn_readlane(key, i);
+    expand_words<kInv, NR, nk, 1u, 0>(lds, b, lane, w, kreg);
     return kreg;
 }
 
@@ -124,10 +167,7 @@ __device__ __forceinline__ uint32_t expand_key(const uint32_t *lds, const uint32
 template <int NR>
 __device__ __forceinline__ uint32_t decrypt_keys(const uint32_t *lds, const Bases &b,
                                                  uint32_t enc) {
-    // The lane index is re-read here, so that the lane-dependent values below
-    // are not kept in registers through the whole launch.
-    uint32_t i = threadIdx.x & 63u;
-    asm volatile("" : "+v"(i));
+    const uint32_t i = fresh_lane();
     const uint32_t src = i < 4 * NR + 4 ? 4 * (NR - i / 4) + (i & 3) : 0;
     const uint32_t w = __builtin_amdgcn_ds_bpermute(int(src * 4), int(enc));
     if (i < 4 || i >= 4 * NR) return w;
@@ -151,16 +191,16 @@ __device__ __forceinline__ void round_key(uint32_t kreg, uint32_t r, uint32_t (&
 // Device key expansion for the message's key size.
 template <bool kInv>
 __device__ __forceinline__ uint32_t schedule_of(const uint32_t *lds, const Bases &b,
-                                                const uint32_t *key, uint32_t nr) {
+                                                uint32_t key, uint32_t nr) {
     uint32_t kreg;
     if (nr == 10) {
-        kreg = expand_key<kInv, 10>(lds, key);
+        kreg = expand_key<kInv, 10>(lds, b, key);
         if constexpr (kInv) kreg = decrypt_keys<10>(lds, b, kreg);
     } else if (nr == 12) {
-        kreg = expand_key<kInv, 12>(lds, key);
+        kreg = expand_key<kInv, 12>(lds, b, key);
         if constexpr (kInv) kreg = decrypt_keys<12>(lds, b, kreg);
     } else {
-        kreg = expand_key<kInv, 14>(lds, key);
+        kreg = expand_key<kInv, 14>(lds, b, key);
         if constexpr (kInv) kreg = decrypt_keys<14>(lds, b, kreg);
     }
     return kreg;
@@ -231,10 +271,7 @@ __device__ __forceinline__ void mid_round_chunk(const uint32_t *lds, const Bases
     uint32_t k[4 * R];
     row_words<kI0>(kq[kX], k, std::make_integer_sequence<int, 4 * R>{});
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) mid_round<kInv>(lds, b, s[j], &k[4 * t]);
-    }
+    for (int t = 0; t < R; ++t) mid_round<kInv>(lds, b, s, &k[4 * t]);
 }
 
 // T_t[x] from the table image in device memory (te = its forward tables),
@@ -244,17 +281,29 @@ __device__ __forceinline__ uint32_t table_s(const uint32_t *te, int t, uint32_t 
     return as_const(te)[__builtin_amdgcn_readfirstlane(uint32_t(t) * 256u + x)];
 }
 
+// The lookups of rounds 1 and 2 of a CTR block that depend on the low byte of its
+// counter (and on key and nonce): `low` holds that byte.
+__device__ __forceinline__ void low_byte_lookups(const uint32_t *lds, const Bases &b,
+                                                 const CtrConsts &cc, uint32_t low,
+                                                 uint32_t (&o)[4]) {
+    const uint32_t v0 = cc.p[0] ^ tlook<3>(lds, (low << 24) ^ cc.kvar, b.t[3]);
+    o[0] = tlook<0>(lds, v0, b.t[0]);
+    o[1] = tlook<3>(lds, v0, b.t[3]);
+    o[2] = tlook<2>(lds, v0, b.t[2]);
+    o[3] = tlook<1>(lds, v0, b.t[1]);
+}
+
 // Rounds 1 and 2 of a CTR step whose 64 * NB counters start at ctr_first, a
 // multiple of 64 * NB (block j of this lane has counter ctr_first + 64 j +
 // lane), so they differ only in their low byte.  Round 1 (Eq. (1)): output
 // words 1..3 and three terms of word 0 are the same for the whole step; in
-// round 2 each output word has one term on word 0 (per block) and three on
-// words 1..3 (per step), read once per step through the scalar cache.
+// round 2 each output word has one term on word 0 (per block, in `kept`) and
+// three on words 1..3 (per step), read once per step through the scalar cache.
 template <int NB>
-__device__ __forceinline__ void ctr_rounds_1_2(const uint32_t *lds, const uint32_t *te,
-                                               const Bases &b, uint32_t kreg,
+__device__ __forceinline__ void ctr_rounds_1_2(const uint32_t *te, uint32_t kreg,
                                                const CtrConsts &cc, uint32_t ctr_first,
-                                               uint32_t lane, uint32_t (&s)[NB][4]) {
+                                               const uint32_t (&kept)[NB][4],
+                                               uint32_t (&s)[NB][4]) {
     const uint32_t w3u = bswap32(ctr_first) ^ cc.kvar;
     const uint32_t u1 = cc.p[1] ^ table_s(te, 2, (w3u >> 16) & 0xFFu);
     const uint32_t u2 = cc.p[2] ^ table_s(te, 1, (w3u >> 8) & 0xFFu);
@@ -275,21 +324,19 @@ __device__ __forceinline__ void ctr_rounds_1_2(const uint32_t *lds, const uint32
                              k2[3], 0u);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const uint32_t w3 = bswap32(ctr_first + uint32_t(j) * 64u + lane) ^ cc.kvar;
-        const uint32_t v0 = cc.p[0] ^ tlook<3>(lds, w3, b.t[3]);
-        s[j][0] = tlook<0>(lds, v0, b.t[0]) ^ c0;
-        s[j][1] = tlook<3>(lds, v0, b.t[3]) ^ c1;
-        s[j][2] = tlook<2>(lds, v0, b.t[2]) ^ c2;
-        s[j][3] = tlook<1>(lds, v0, b.t[1]) ^ c3;
+        s[j][0] = kept[j][0] ^ c0;
+        s[j][1] = kept[j][1] ^ c1;
+        s[j][2] = kept[j][2] ^ c2;
+        s[j][3] = kept[j][3] ^ c3;
     }
 }
 
 // The rounds of one step: NB blocks per lane, block j of this lane at tile
 // offset step_off + 64 j + lane (base is the same offset from the message's
-// block 0), then the mode's output XOR and the store.
+// block 0), then the mode's output XOR and the store.  (Whole CTR steps of more
+// than one block per lane have their own, below.)
 template <bool kInv, int NB, int kPolicy>
-__device__ __forceinline__ void crypt_step(const uint32_t *lds, const uint32_t *te, const Bases &b,
-                                           uint32_t kreg,
+__device__ __forceinline__ void crypt_step(const uint32_t *lds, const Bases &b, uint32_t kreg,
                                            const uint32_t (&kq)[3], uint32_t nr, bool ctr,
                                            const CtrConsts &cc,
                                            const DevMsg &m, uint32_t cbc_mask, uint64_t base,
@@ -297,88 +344,50 @@ __device__ __forceinline__ void crypt_step(const uint32_t *lds, const uint32_t *
                                            const uint4 (&prev)[NB], rsrc_t rout) {
     uint32_t s[NB][4];
     uint32_t rk[4];
-    // The rounds up to the last: the standard order, or for whole CTR steps
-    // rounds 1 and 2 with their per-step lookups shared.
-    auto standard_rounds = [&]() {
-        round_key(kreg, 0, rk);
+            round_key(kreg, 0, rk);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const uint64_t idx = base + uint64_t(j) * 64u + lane;
-            if (ctr) {
-                counter_round1(lds, b, cc, m.ctr0 + uint32_t(idx), s[j]);
+            for (int j = 0; j < NB; ++j) {
+                const uint64_t idx = base + uint64_t(j) * 64u + lane;
+                if (ctr) {
+                    counter_round1(lds, b, cc, m.ctr0 + uint32_t(idx), s[j]);
+                } else {
+                    s[j][0] = d[j].x ^ rk[0];
+                    s[j][1] = d[j].y ^ rk[1];
+                    s[j][2] = d[j].z ^ rk[2];
+                    s[j][3] = d[j].w ^ rk[3];
+                }
+            }
+            if (!ctr) {
+                round_key(kreg, 1, rk);
+                mid_round<kInv>(lds, b, s, rk);
+            }
+            if constexpr (NB > 1) {
+                // Rounds 2 .. nr - 1 as one straight sequence of 12 rounds that
+                // AES-192 enters at its third round and AES-128 at its fifth (round
+                // q + nr - 13 at position q), in chunks of two or four rounds whose
+                // round keys come from the per-tile key registers by row broadcast.
+                // Unlike a rolled loop, or round keys read into SGPRs round by round,
+                // this lets the compiler overlap more of the rounds' table reads.
+                switch (nr) {
+                    case 14:
+                        mid_round_chunk<kInv, NB, 1, 2>(lds, b, kq, s);
+                        [[fallthrough]];
+                    case 12:
+                        mid_round_chunk<kInv, NB, 3, 2>(lds, b, kq, s);
+                        [[fallthrough]];
+                    default:
+                        mid_round_chunk<kInv, NB, 5, 4>(lds, b, kq, s);
+                        mid_round_chunk<kInv, NB, 9, 4>(lds, b, kq, s);
+                }
             } else {
-                s[j][0] = d[j].x ^ rk[0];
-                s[j][1] = d[j].y ^ rk[1];
-                s[j][2] = d[j].z ^ rk[2];
-                s[j][3] = d[j].w ^ rk[3];
-            }
-        }
-        if (!ctr) {
-            round_key(kreg, 1, rk);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) mid_round<kInv>(lds, b, s[j], rk);
-        }
-        if constexpr (NB > 1) {
-            // Rounds 2 .. nr - 1 as one straight sequence of 12 rounds that
-            // AES-192 enters at its third round and AES-128 at its fifth (round
-            // q + nr - 13 at position q), in chunks of two or four rounds whose
-            // round keys come from the per-tile key registers by row broadcast.
-            // Unlike a rolled loop, or round keys read into SGPRs round by round,
-            // this lets the compiler overlap more of the rounds' table reads.
-            switch (nr) {
-                case 14:
-                    mid_round_chunk<kInv, NB, 1, 2>(lds, b, kq, s);
-                    [[fallthrough]];
-                case 12:
-                    mid_round_chunk<kInv, NB, 3, 2>(lds, b, kq, s);
-                    [[fallthrough]];
-                default:
-                    mid_round_chunk<kInv, NB, 5, 4>(lds, b, kq, s);
-                    mid_round_chunk<kInv, NB, 9, 4>(lds, b, kq, s);
-            }
-        } else {
 #pragma unroll 1
-            for (uint32_t r = 2; r < nr; ++r) {
-                round_key(kreg, r, rk);
-#pragma unroll
-                for (int j = 0; j < NB; ++j) mid_round<kInv>(lds, b, s[j], rk);
+                for (uint32_t r = 2; r < nr; ++r) {
+                    round_key(kreg, r, rk);
+                    mid_round<kInv>(lds, b, s, rk);
+                }
             }
-        }
-    };
-    if constexpr (!kInv && NB > 1) {
-        if (ctr) {
-            // A whole CTR step starts at a counter that is a multiple of
-            // 64 * NB (the tile's blocks before the first such counter run
-            // in 64-block groups), so rounds 1 and 2 take 5 table reads per
-            // block and 15 scalar loads per step, and the sequence enters at
-            // round 3.
-            ctr_rounds_1_2<NB>(lds, te, b, kreg, cc, m.ctr0 + uint32_t(base), lane, s);
-            switch (nr) {
-                case 14:
-                    mid_round_chunk<false, NB, 2, 2>(lds, b, kq, s);
-                    [[fallthrough]];
-                case 12:
-                    mid_round_chunk<false, NB, 4, 1>(lds, b, kq, s);
-                    mid_round_chunk<false, NB, 5, 1>(lds, b, kq, s);
-                    [[fallthrough]];
-                default:
-                    mid_round_chunk<false, NB, 6, 3>(lds, b, kq, s);
-                    mid_round_chunk<false, NB, 9, 4>(lds, b, kq, s);
-            }
-        } else {
-            standard_rounds();
-        }
-    } else {
-        standard_rounds();
-    }
     round_key(kreg, nr, rk);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        if constexpr (kInv)
-            last_round_inv(lds, b, s[j], rk);
-        else
-            last_round_fwd(lds, b, s[j], rk);
-    }
+    last_round<kInv>(lds, b, s, rk);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         uint4 o = make_uint4(s[j][0], s[j][1], s[j][2], s[j][3]);
@@ -411,77 +420,42 @@ __device__ __forceinline__ void crypt_step(const uint32_t *lds, const uint32_t *
     }
 }
 
-// One tile: nr rounds on BPL blocks per lane per step.  The round loop is not
-// unrolled and takes nr at run time: one short loop body serves all key
-// sizes, so the code a workgroup runs fits the instruction cache even when
-// each CU executes it only once (small batches).  Whole steps of 64 * BPL
-// blocks run with the next step's blocks loaded ahead; the blocks after the
-// last whole step run 64 at a time, one per lane, so a short tile or a
-// tile's ragged end costs rounds only for the waves' 64-block groups that
-// hold blocks.
-// A wave's last expanded key schedule (lane i holds word i), with the key
-// slot and round count it was expanded for.
-struct KeyCache {
-    uint32_t slot = 0xFFFFFFFFu;
-    uint32_t nr = 0;
-    uint32_t kreg = 0;
-};
+// Raw key words of a message (lane i: word i), or its resident schedule (lane i:
+// word i of the set's direction).
+template <bool kInv>
+__device__ __forceinline__ uint32_t load_schedule(const uint32_t *sched, uint32_t slot, uint32_t nr) {
+    const uint32_t lane = fresh_lane();
+    const uint32_t *w = sched + uint64_t(slot) * kSchedWords + (kInv ? 64u : 0u);
+    return lane < 4u * (nr + 1) ? w[lane] : 0u;
+}
 
-template <bool kInv, int BPL, int kPolicy = 0>
+template <bool kInv>
+__device__ __forceinline__ uint32_t load_key(const BatchParams &p, uint32_t slot, uint32_t nr) {
+    if (p.sched) return load_schedule<kInv>(p.sched, slot, nr);
+    const uint32_t lane = fresh_lane();
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(p.keys + 32ull * slot);
+    return lane < nr - 6u ? w[lane] : 0u;
+}
+
+// Runs one tile of message m, whose key load_key() gave.  Whole steps of
+// 64 * BPL blocks run the middle rounds as one straight sequence for all key
+// sizes; the blocks outside them run 64 at a time, one per lane, in a rolled
+// round loop, so a short tile or a tile's ragged end costs rounds only for the
+// 64-block groups that hold blocks.  after_key and before_steps are called at
+// two points of the tile's start, a memory latency apart (the drain loop fetches
+// its next tile's descriptors there).
+//
+// A short tile is bound by this start, not by its rounds: data loaded before the
+// key is expanded, an expansion of about 1 us and the descriptors fetched ahead
+// took 65,536 messages of up to 16 KiB from 225 to 210 us, and 8 of 4 KiB
+// from 11.6 to 11.0 us.
+template <bool kInv, int BPL, int kPolicy = 0, class F, class G>
 __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, const BatchParams &p,
-                                         const DevMsg &m, const Tile &tile,
-                                         KeyCache *kc = nullptr) {
+                                         const DevMsg &m, const Tile &tile, uint32_t key,
+                                         F &&after_key, G &&before_steps) {
     const uint32_t nr = m.nr;
-    uint32_t kreg;
-    if (kc != nullptr && kc->slot == m.key_slot && kc->nr == nr) {
-        // The wave's previous tile had the same key (consecutive tiles of one
-        // message, in the queue's order): no expansion.
-        kreg = kc->kreg;
-    } else if (p.sched) {
-        // Resident schedule: lane i loads word i (encryption words first,
-        // then the equivalent-inverse-cipher words).
-        const uint32_t lane = threadIdx.x & 63u;
-        const uint32_t *w = p.sched + uint64_t(m.key_slot) * kSchedWords + (kInv ? 64u : 0u);
-        kreg = lane < 4u * (nr + 1) ? w[lane] : 0u;
-    } else {
-        const uint32_t *key = reinterpret_cast<const uint32_t *>(p.keys + 32ull * m.key_slot);
-        kreg = schedule_of<kInv>(lds, b, key, nr);
-        if (kc != nullptr) *kc = KeyCache{m.key_slot, nr, kreg};
-    }
-
+    const uint32_t lane = fresh_lane();
     const bool ctr = !kInv && m.mode == AESGPU_MODE_CTR;
-    CtrConsts cc{};
-    if (!kInv && ctr) {
-        // Counter words 0..2 are the nonce for every block of the message.
-        uint32_t k0[4], k1[4];
-        round_key(kreg, 0, k0);
-        round_key(kreg, 1, k1);
-        uint32_t x[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) x[c] = m.nonce[c] ^ k0[c];
-        cc.kvar = k0[3];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            uint32_t v = k1[c];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int i = (c + k) & 3;
-                if (i != 3) v ^= table_u(lds, k, (x[i] >> (8 * k)) & 0xFFu);
-            }
-            cc.p[c] = v;
-        }
-    }
-
-    const uint32_t lane = threadIdx.x & 63u;
-    // Round keys of the whole steps' middle-round sequence, 16 words per
-    // register and row (lane permutes, once per tile): position q runs round
-    // q + nr - 13, whose word c is lane 4 (q + nr - 13) + c of the schedule.
-    const uint32_t *te = p.tables + kTe;   // forward tables in device memory
-    uint32_t kq[3];
-#pragma unroll
-    for (int x = 0; x < 3; ++x)
-        kq[x] = uint32_t(__builtin_amdgcn_ds_bpermute(
-            int((4u * (4u * x + 1u) + (lane & 15u) + 4u * (nr - 13u)) * 4u), int(kreg)));
     const uint4 *in = reinterpret_cast<const uint4 *>(p.in + m.in_off);
     uint4 *out = reinterpret_cast<uint4 *>(p.out + m.out_off);
     const uint64_t first = tile.first_block;
@@ -507,8 +481,8 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
     // are loaded while the current step is computed).  The whole-step loop
     // loads through resources that end at its last step, so its look-ahead
     // past that step reads nothing.
-    const rsrc_t rin = buffer_rsrc(in + first, uniform(16u * h1));
-    const rsrc_t rout = buffer_rsrc(out + first, 16u * n_blk);
+    // (Whole CTR steps look nothing ahead and load through rin_all.)
+    const rsrc_t rin = buffer_rsrc(in + first, uniform(BPL > 1 && ctr ? 0u : 16u * h1));
     // CBC decryption (Eq. (2)): every block is XORed with the ciphertext
     // block before it (the IV for block 0), read through a resource that
     // starts one block before the tile.  ECB-decrypt tiles issue the same
@@ -519,60 +493,22 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
     const rsrc_t rprev =
         buffer_rsrc(in + pbase, uniform(cbc && h1 ? 16u * (h1 + 1u - pshift) : 0u));
     const uint32_t cbc_mask = cbc ? ~0u : 0u;
-    // The blocks outside the whole steps (64 at a time, one per lane) and a
-    // CTR message's partial last block run first: nothing they need stays
-    // live through the whole steps' rounds, which keeps the SGPRs in use there
-    // few enough for the compiler to keep many table reads in flight.
-    if constexpr (BPL > 1) {
-        if (h0 > 0 || h1 < n_blk) {
-            const rsrc_t rin_all = buffer_rsrc(in + first, uniform(16u * n_blk));
-            const rsrc_t rprev_all =
-                buffer_rsrc(in + pbase, uniform(cbc ? 16u * (n_blk + 1u - pshift) : 0u));
-            // Groups start at 0 while below h0 (their stores end at h0), then
-            // at h1.
-            uint32_t g = h0 > 0 ? 0u : h1;
-            uint32_t stop = h0 > 0 ? h0 : n_blk;
-            while (g < stop) {
-                asm volatile("" : "+v"(kreg));
-                uint4 d[1], prev[1];
-                d[0] = tile_load16<kPolicy>(rin_all, (g + lane) * 16u);
-                prev[0] = make_uint4(0, 0, 0, 0);
-                if constexpr (kInv)
-                    prev[0] = tile_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
-                const rsrc_t rout_g = buffer_rsrc(out + first, uniform(16u * stop));
-                crypt_step<kInv, 1, kPolicy>(lds, te, b, kreg, kq, nr, ctr, cc, m, cbc_mask,
-                                             first + g, g, lane, d, prev, rout_g);
-                g += 64u;
-                if (g >= stop && stop != n_blk) {
-                    g = h1;
-                    stop = n_blk;
-                }
-            }
-        }
-    }
-    if constexpr (!kInv) {
-        // Partial last block of a CTR message (it lies in the message's last
-        // tile): every lane computes its keystream, lane q < tail writes byte q.
-        if (ctr && m.tail && end > m.n_full) {
-            uint32_t s[4];
-            uint32_t rk[4];
-            counter_round1(lds, b, cc, m.ctr0 + uint32_t(m.n_full), s);
-#pragma unroll 1
-            for (uint32_t r = 2; r < nr; ++r) {
-                round_key(kreg, r, rk);
-                mid_round<false>(lds, b, s, rk);
-            }
-            round_key(kreg, nr, rk);
-            last_round_fwd(lds, b, s, rk);
-            if (lane < m.tail) {
-                const uint8_t *src = reinterpret_cast<const uint8_t *>(in + m.n_full);
-                uint8_t *dst = reinterpret_cast<uint8_t *>(out + m.n_full);
-                const uint32_t w = lane < 4 ? s[0] : lane < 8 ? s[1] : lane < 12 ? s[2] : s[3];
-                dst[lane] = src[lane] ^ uint8_t(w >> (8 * (lane & 3u)));
-            }
-        }
-    }
+    // The blocks outside the whole steps run 64 at a time, one per lane, from g
+    // on: first those from 0 while below h0 (their stores end at h0), then
+    // those from h1.
+    uint32_t g = h0 > 0 ? 0u : h1;
+    uint32_t stop = h0 > 0 ? h0 : n_blk;
+    const rsrc_t rin_all = buffer_rsrc(in + first, uniform(16u * n_blk));
+    const rsrc_t rprev_all =
+        buffer_rsrc(in + pbase, uniform(cbc ? 16u * (n_blk + 1u - pshift) : 0u));
+    // The first blocks are loaded before the key is expanded, which takes about
+    // as long as they do.
     uint4 next[BPL], next_prev[BPL];
+    uint4 gd = make_uint4(0, 0, 0, 0), gp = make_uint4(0, 0, 0, 0);
+    if constexpr (BPL > 1) {
+        gd = tile_load16<kPolicy>(rin_all, (g + lane) * 16u);
+        if constexpr (kInv) gp = tile_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
+    }
 #pragma unroll
     for (int j = 0; j < BPL; ++j)
         next[j] = tile_load16<kPolicy>(rin, (h0 + uint32_t(j) * 64u + lane) * 16u);
@@ -580,6 +516,144 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
 #pragma unroll
         for (int j = 0; j < BPL; ++j)
             next_prev[j] = tile_load16<kPolicy>(rprev, (h0 + uint32_t(j) * 64u + lane - pshift) * 16u);
+    }
+
+    // (The resident kernel has schedules only.)
+    uint32_t kreg = key;
+    if (kPolicy != kCoherent && !p.sched) kreg = schedule_of<kInv>(lds, b, key, nr);
+    after_key();
+
+    CtrConsts cc{};
+    if (!kInv && ctr) {
+        // Counter words 0..2 are the nonce for every block of the message.
+        uint32_t k0[4], k1[4];
+        round_key(kreg, 0, k0);
+        round_key(kreg, 1, k1);
+        uint32_t x[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[c] = m.nonce[c] ^ k0[c];
+        cc.kvar = k0[3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            uint32_t v = k1[c];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = (c + k) & 3;
+                if (i != 3) v ^= table_u(lds, k, (x[i] >> (8 * k)) & 0xFFu);
+            }
+            cc.p[c] = v;
+        }
+    }
+
+    // Round keys of the whole steps' middle-round sequence, 16 words per
+    // register and row (lane permutes, once per tile): position q runs round
+    // q + nr - 13, whose word c is lane 4 (q + nr - 13) + c of the schedule.
+    const uint32_t *te = p.tables + kTe;   // forward tables in device memory
+    uint32_t kq[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+        kq[x] = uint32_t(__builtin_amdgcn_ds_bpermute(
+            int((4u * (4u * x + 1u) + (lane & 15u) + 4u * (nr - 13u)) * 4u), int(kreg)));
+    const rsrc_t rout = buffer_rsrc(out + first, 16u * n_blk);
+    // The blocks outside the whole steps and a CTR message's partial last block
+    // run first: nothing they need stays live through the whole steps' rounds,
+    // which keeps the SGPRs in use there few enough for the compiler to keep
+    // many table reads in flight.
+    if constexpr (BPL > 1) {
+        while (g < stop) {
+            asm volatile("" : "+v"(kreg));
+            const uint32_t now = g;
+            const rsrc_t rout_g = buffer_rsrc(out + first, uniform(16u * stop));
+            const uint4 d[1] = {gd}, prev[1] = {gp};
+            g += 64u;
+            if (g >= stop && stop != n_blk) {
+                g = h1;
+                stop = n_blk;
+            }
+            gd = tile_load16<kPolicy>(rin_all, (g + lane) * 16u);
+            if constexpr (kInv) gp = tile_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
+            crypt_step<kInv, 1, kPolicy>(lds, b, kreg, kq, nr, ctr, cc, m, cbc_mask,
+                                         first + now, now, lane, d, prev, rout_g);
+        }
+    }
+    if constexpr (!kInv) {
+        // Partial last block of a CTR message (it lies in the message's last
+        // tile): every lane computes its keystream, lane q < tail writes byte q.
+        if (ctr && m.tail && end > m.n_full) {
+            uint32_t s[1][4];
+            uint32_t rk[4];
+            counter_round1(lds, b, cc, m.ctr0 + uint32_t(m.n_full), s[0]);
+#pragma unroll 1
+            for (uint32_t r = 2; r < nr; ++r) {
+                round_key(kreg, r, rk);
+                mid_round<false>(lds, b, s, rk);
+            }
+            round_key(kreg, nr, rk);
+            last_round<false>(lds, b, s, rk);
+            if (lane < m.tail) {
+                const uint8_t *src = reinterpret_cast<const uint8_t *>(in + m.n_full);
+                uint8_t *dst = reinterpret_cast<uint8_t *>(out + m.n_full);
+                const uint32_t w =
+                    lane < 4 ? s[0][0] : lane < 8 ? s[0][1] : lane < 12 ? s[0][2] : s[0][3];
+                dst[lane] = src[lane] ^ uint8_t(w >> (8 * (lane & 3u)));
+            }
+        }
+    }
+    before_steps();
+    if constexpr (!kInv && BPL > 1) {
+        if (ctr) {
+            // Whole CTR steps start at counters that are multiples of 64 * BPL:
+            // rounds 1 and 2 take 15 scalar loads per step and at 2 blocks per
+            // lane 5 table reads per block.  At 4 the low byte of a lane's
+            // counter is the same in every step, and these reads are made once
+            // per tile; their registers are the look-ahead's, which CTR does
+            // not need, as its input is XORed in last.
+            constexpr bool kKept = BPL == 4;
+            uint32_t kept[BPL][4];
+            const uint32_t ctr_first = m.ctr0 + uint32_t(first);
+#pragma unroll
+            for (int j = 0; j < BPL; ++j)
+                if constexpr (kKept)
+                    low_byte_lookups(lds, b, cc, uint32_t(j) * 64u + lane, kept[j]);
+            for (uint32_t step_off = h0; step_off < h1; step_off += kStep) {
+                asm volatile("" : "+v"(kreg));
+                uint4 d[BPL];
+#pragma unroll
+                for (int j = 0; j < BPL; ++j) {
+                    d[j] = tile_load16<kPolicy>(rin_all, (step_off + uint32_t(j) * 64u + lane) * 16u);
+                    if constexpr (!kKept)
+                        low_byte_lookups(
+                            lds, b, cc,
+                            (ctr_first + step_off + uint32_t(j) * 64u + lane) & 0xFFu, kept[j]);
+                }
+                uint32_t s[BPL][4];
+                ctr_rounds_1_2<BPL>(te, kreg, cc, ctr_first + step_off, kept, s);
+                // The sequence of crypt_step, entered at round 3.
+                switch (nr) {
+                    case 14:
+                        mid_round_chunk<false, BPL, 2, 2>(lds, b, kq, s);
+                        [[fallthrough]];
+                    case 12:
+                        mid_round_chunk<false, BPL, 4, 1>(lds, b, kq, s);
+                        mid_round_chunk<false, BPL, 5, 1>(lds, b, kq, s);
+                        [[fallthrough]];
+                    default:
+                        mid_round_chunk<false, BPL, 6, 3>(lds, b, kq, s);
+                        mid_round_chunk<false, BPL, 9, 4>(lds, b, kq, s);
+                }
+                uint32_t rk[4];
+                round_key(kreg, nr, rk);
+                last_round<false>(lds, b, s, rk);
+#pragma unroll
+                for (int j = 0; j < BPL; ++j)
+                    tile_store16<kPolicy>(rout, (step_off + uint32_t(j) * 64u + lane) * 16u,
+                                          make_uint4(s[j][0] ^ d[j].x, s[j][1] ^ d[j].y,
+                                                     s[j][2] ^ d[j].z, s[j][3] ^ d[j].w));
+            }
+            return;
+        }
+    }
+    if constexpr (kInv) {
         // Message block 0 can only be the first whole step's slot 0 of lane
         // 0 (its predecessor load read nothing): its predecessor is the IV.
         if (first + h0 == 0 && lane == 0)
@@ -613,8 +687,8 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
                     rprev, (step_off + kStep + uint32_t(j) * 64u + lane - pshift) * 16u);
             }
         }
-        crypt_step<kInv, BPL, kPolicy>(lds, te, b, kreg, kq, nr, ctr, cc, m, cbc_mask, first + step_off,
-                                       step_off, lane, d, prev, rout);
+        crypt_step<kInv, BPL, kPolicy>(lds, b, kreg, kq, nr, BPL == 1 && ctr, cc, m, cbc_mask,
+                                       first + step_off, step_off, lane, d, prev, rout);
     }
 }
 
@@ -644,7 +718,7 @@ __device__ __forceinline__ uint32_t quad_rot(uint32_t v) {
 // after round, so what counts is its length: with the permutations before the
 // lookups, as moves of the state words, it had three more steps and the
 // wait between a write and a DPP read of it.  The last round takes the
-// S-box bytes from the T tables as last_round_fwd does.
+// S-box bytes from the T tables as last_lookups does.
 template <bool kLast>
 __device__ __forceinline__ uint32_t quad_round(const uint32_t *lds, const Bases &b, uint32_t s,
                                                uint32_t k) {
@@ -811,56 +885,112 @@ constexpr uint32_t kDryWord = kFwdWords + 1;
 // 4096 waves that each find the queue empty once take 53 us.  Batches of a few
 // hundred microseconds therefore have no dynamic tiles at all, and otherwise
 // the first wave that finds none left tells its workgroup.
+// Index in the queue of row `row` of workgroup wg's list, n workgroups having one.
+__device__ __forceinline__ uint32_t listed_tile(uint32_t row, uint32_t n, uint32_t wg) {
+    return row * n + ((row & 1u) ? n - 1u - wg : wg);
+}
+
+// A tile with what its start needs: its message's descriptor and key words.
+struct Work {
+    Tile tile;
+    DevMsg m;
+    uint32_t key;   // load_key()'s
+};
+
+// Scalar loads (the index is wave-uniform and nothing writes the descriptors
+// during a launch), so every field is uniform.
+template <bool kInv>
+__device__ __forceinline__ void load_work(Work &w, const BatchParams &p, uint32_t at) {
+    w.tile = load_uniform(p.tiles[kInv ? 1 : 0] + at);
+    w.m = load_uniform(p.msgs + w.tile.msg);
+    w.key = load_key<kInv>(p, w.m.key_slot, w.m.nr);
+}
+
+// The wave's words of a descriptor, word i in lanes i, i + N, ...
+template <class T>
+__device__ __forceinline__ uint32_t load_words(const T *src) {
+    constexpr uint32_t kWords = sizeof(T) / 4;
+    static_assert((kWords & (kWords - 1)) == 0, "a power of two");
+    return reinterpret_cast<const uint32_t *>(src)[fresh_lane() & (kWords - 1)];
+}
+
+template <class T>
+__device__ __forceinline__ T from_words(uint32_t v) {
+    T t;
+    uint32_t *d = reinterpret_cast<uint32_t *>(&t);
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) d[i] = __builtin_amdgcn_readlane(v, i);
+    return t;
+}
+
+// The tiles a wave has pulled from behind the lists.
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+struct PulledRun {
+    uint32_t t = 0, end = 0;
+
+    // The next tile's index, kNone if there is none (any more).
+    __device__ __forceinline__ uint32_t next(uint32_t *lds, const BatchParams &p, int set) {
+        const uint32_t n_tiles = p.n_tiles[set];
+        t = uniform(t);
+        if (t >= end) {
+            t = kNone;
+            const uint32_t dry = __hip_atomic_load(lds + kDryWord, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (p.n_static[set] < n_tiles && !(uniform(dry) >> 16)) {
+                // One atomic per run of `pull` consecutive tiles (similar in
+                // size, the queue being sorted).
+                uint32_t c = 0;
+                if ((threadIdx.x & 63u) == 0)
+                    c = atomicAdd(&p.counters[kQueueStride * set], p.pull[set]);
+                t = p.n_static[set] + uniform(c);
+                end = t + p.pull[set];
+                if (t >= n_tiles && (threadIdx.x & 63u) == 0)
+                    __hip_atomic_fetch_or(lds + kDryWord, 0x10000u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        return t < n_tiles ? t++ : kNone;
+    }
+};
+
 template <bool kInv, int BPL>
-__device__ __forceinline__ void drain_queue(uint32_t *lds, const Bases &b, uint32_t wg, bool own) {
+__device__ __forceinline__ void drain_queue(uint32_t *lds, const Bases &b, uint32_t wg, bool listed,
+                                            Work &w) {
     constexpr int set = kInv ? 1 : 0;
-    uint32_t row = threadIdx.x >> 6;
-    uint32_t t = 0, run_end = 0;  // the run of tiles taken by the last pull
-    KeyCache kc;
+    bool have = listed;           // w is the next tile, from the list if `listed`
+    PulledRun run;
     for (;;) {
         // The launch's parameters are read again from the kernel-argument
         // segment for every tile (scalar loads that hit the scalar cache)
         // rather than held in SGPRs through the tile: with fewer SGPRs in use
         // the compiler keeps many more table reads in flight in the rounds.
         const BatchParams &p = kernel_params();
-        const DevMsg *__restrict__ msgs = p.msgs;
-        const Tile *__restrict__ tiles = p.tiles[set];
-        uint32_t at;
-        if (own) {
-            row = __builtin_amdgcn_readfirstlane(row);
-            const uint32_t n = p.n_wg[set];
-            at = row * n + ((row & 1u) ? n - 1u - wg : wg);
-            own = at < p.n_static[set];
+        if (!have) {
+            const uint32_t at = run.next(lds, p, set);
+            if (at == kNone) break;
+            load_work<kInv>(w, p, at);
         }
-        if (!own) {
-            t = __builtin_amdgcn_readfirstlane(t);
-            if (t >= run_end) {
-                if (p.n_static[set] >= p.n_tiles[set]) break;  // no dynamic tiles at all
-                const uint32_t dry = __hip_atomic_load(lds + kDryWord, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (uniform(dry) >> 16) break;
-                // One atomic per run of `pull` consecutive tiles (similar in
-                // size, the queue being sorted).
-                uint32_t c = 0;
-                if ((threadIdx.x & 63u) == 0)
-                    c = atomicAdd(&p.counters[kQueueStride * set], p.pull[set]);
-                t = p.n_static[set] + __builtin_amdgcn_readfirstlane(c);
-                run_end = t + p.pull[set];
-            }
-            at = t++;
-            if (at >= p.n_tiles[set]) {
-                if ((threadIdx.x & 63u) == 0)
-                    __hip_atomic_fetch_or(lds + kDryWord, 0x10000u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_WORKGROUP);
-                break;
-            }
-        }
-        // Scalar loads (the index is wave-uniform and nothing writes the
-        // descriptors during a launch), so every field is uniform.
-        const Tile tile = load_uniform(tiles + at);
-        const DevMsg m = load_uniform(msgs + tile.msg);
-        run_tile<kInv, BPL>(lds, b, p, m, tile, &kc);
-        if (own) row = kWG / 64 + claim_share(lds + kRowWord);
+        // The next row is claimed before this tile runs, and its descriptors
+        // and key are fetched one after the other meanwhile (a word per lane,
+        // three registers).  Fetched when their turn came, the three loads,
+        // each needing the one before, stood at the start of every tile.
+        uint32_t at = p.n_static[set];
+        if (listed) at = listed_tile(kWG / 64 + claim_share(lds + kRowWord), p.n_wg[set], wg);
+        listed = at < p.n_static[set];
+        const uint32_t vt = load_words(p.tiles[set] + (listed ? at : 0u));
+        uint32_t vm = 0, vk = 0;
+        run_tile<kInv, BPL>(
+            lds, b, p, w.m, w.tile, w.key,
+            [&] { vm = load_words(p.msgs + __builtin_amdgcn_readlane(vt, 0)); },
+            [&] {
+                const DevMsg m = from_words<DevMsg>(vm);
+                vk = load_key<kInv>(p, m.key_slot, m.nr);
+            });
+        w.tile = from_words<Tile>(vt);
+        w.m = from_words<DevMsg>(vm);
+        w.key = vk;
+        have = listed;
     }
 }
 
@@ -884,7 +1014,7 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
         // device memory with a release and an acquire at agent scope, the
         // decision cost far more than the staging: each is a write-back or an
         // invalidation of the XCD's L2, and with 256 workgroups doing both the
-        // table reads that follow missed again and again.  The tables were
+        // table reads that follow missed again and again.  The tables were then
         // staged 33 us after the start of a launch of 256 workgroups and 14 us
         // after that of 97.)
         const bool own = pass == 0 && wg_in_set < p.n_static[set];
@@ -892,8 +1022,8 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
         if (!work) {
             __syncthreads();  // all waves are past the previous queue
             if (threadIdx.x == 0) {
-                const uint32_t pulled = __hip_atomic_load(&p.counters[kQueueStride * set], __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t pulled = __hip_atomic_load(
+                    &p.counters[kQueueStride * set], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 lds[0] = p.n_static[set] < p.n_tiles[set] &&
                                  pulled < p.n_tiles[set] - p.n_static[set]
                              ? 1u
@@ -905,17 +1035,29 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
         }
         if (!work) continue;
         // The staging's indices and addresses are recomputed here rather than
-        // kept in registers through the whole launch.
+        // kept in registers through the whole launch.  The wave's first tile is
+        // fetched between the staging's loads and its LDS writes.
         const uint32_t *tables = p.tables;
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+s"(tables), "+v"(tid));
+        const uint32_t at = listed_tile(uniform(tid >> 6), p.n_wg[set], wg_in_set);
+        const bool listed = own && at < p.n_static[set];
+        Work w{};
         if (set == 0) {
-            if (tid < 2) lds[kRowWord + tid] = 0u;   // published by the staging's barrier
-            stage_tables_tid<false>(lds, tables, tid);
-            drain_queue<false, BPL>(lds, b, wg_in_set, own);
+            const TableWords<false> words = load_tables<false>(tables, tid);
+            if (listed) load_work<false>(w, p, at);
+            if (tid < 2) lds[kRowWord + tid] = 0u;   // published by the barrier
+            write_tables(lds, words, tid);
+            drain_queue<false, BPL>(lds, b, wg_in_set, listed, w);
         } else {
-            stage_tables_tid<true>(lds, tables, tid);
-            drain_queue<true, BPL>(lds, b, wg_in_set, own);
+            const TableWords<true> words = load_tables<true>(tables, tid);
+            if (listed) load_work<true>(w, p, at);
+            write_tables(lds, words, tid);
+            // At 4 blocks per lane a step's ciphertext for Eq. (2) does not
+            // fit the registers beside the table reads in flight.  (Batches of
+            // ECB and CBC decryption, us at 2 / 4 blocks per lane: 4,096
+            // messages up to 16 KiB 37 / 51, 7,459 up to 922 KB 543 / 575.)
+            drain_queue<true, BPL == 4 ? 2 : BPL>(lds, b, wg_in_set, listed, w);
         }
     }
     // The last workgroup to finish zeroes the two queue counters (and the
@@ -932,7 +1074,8 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
                                                        __HIP_MEMORY_SCOPE_AGENT);
         if (before == gridDim.x - 1) {
             __hip_atomic_store(&p.counters[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&p.counters[kQueueStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&p.counters[kQueueStride], 0u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -1101,7 +1244,9 @@ __device__ void serve_ring(const uint32_t *lds, const Bases &b, const ResidentLa
             // producer left it and its output is visible device-wide once the
             // stores are complete, with no L2 invalidation or write-back (a
             // fence at this scope costs one per tile, and those serialise).
-            run_tile<kInv, BPL, kCoherent>(lds, b, bp, m, tile);
+            run_tile<kInv, BPL, kCoherent>(lds, b, bp, m, tile,
+                                           load_schedule<kInv>(p.sched, m.key_slot, m.nr),
+                                           [] {}, [] {});
             // The tile is counted once its stores are complete.  The slot's
             // counter only grows (modulo 2^32); the record holds the count at
             // which this request is complete, and the wave that reaches it
@@ -1200,7 +1345,8 @@ int enqueue_t(const BatchLaunch &L, hipStream_t s) {
         if (!n_wg[q]) continue;
         const uint64_t rows = (uint64_t(L.n_tiles[q]) + n_wg[q] - 1) / n_wg[q];
         uint64_t listed = rows;
-        if (L.blocks[q] / n_wg[q] > kListBlocks) listed = std::max<uint64_t>(L.head[q] / n_wg[q], kWaves);
+        if (L.blocks[q] / n_wg[q] > kListBlocks)
+            listed = std::max<uint64_t>(L.head[q] / n_wg[q], kWaves);
         listed = std::min<uint64_t>(listed, kMaxRows);
         n_static[q] = uint32_t(std::min<uint64_t>(listed * n_wg[q], L.n_tiles[q]));
         const uint32_t dyn = L.n_tiles[q] - n_static[q];

@@ -74,54 +74,78 @@ __device__ __forceinline__ uint32_t merge4_low_xor(uint32_t v0, uint32_t v1, uin
     return xor3(lo, hi, k);
 }
 
-// One middle round, Eq. (1).  Forward: output word c reads byte k of word
-// (c + k) mod 4.  Inverse (equivalent inverse cipher): word (c - k) mod 4.
+// Rounds of NB blocks held by a lane.  Every function makes the lookups of block
+// j + 1 before it combines those of block j, and all 16 of a block before it
+// combines any.  The compiler's scheduler finds such an order by itself only
+// where it keeps within its register limits from the start; where it does not,
+// it goes back to the order written here, and with each output word's four
+// lookups followed by its XORs a wave had only 3 to 5 reads in flight.
 template <bool kInv>
-__device__ __forceinline__ void mid_round(const uint32_t *lds, const Bases &b, uint32_t (&s)[4],
+__device__ __forceinline__ void mid_lookups(const uint32_t *lds, const Bases &b,
+                                            const uint32_t (&s)[4], uint32_t (&v)[4][4]) {
+    // One middle round, Eq. (1).  Forward: output word c reads byte k of word
+    // (c + k) mod 4.  Inverse (equivalent inverse cipher): word (c - k) mod 4.
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        v[c][0] = tlook<0>(lds, s[c], b.t[0]);
+        v[c][1] = tlook<1>(lds, s[(kInv ? c + 3 : c + 1) & 3], b.t[1]);
+        v[c][2] = tlook<2>(lds, s[(c + 2) & 3], b.t[2]);
+        v[c][3] = tlook<3>(lds, s[(kInv ? c + 1 : c + 3) & 3], b.t[3]);
+    }
+}
+
+template <bool kInv>
+__device__ __forceinline__ void last_lookups(const uint32_t *lds, const Bases &b,
+                                             const uint32_t (&s)[4], uint32_t (&v)[4][4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        if constexpr (kInv) {
+            // InvSubBytes + InvShiftRows.
+            v[c][0] = islook<0>(lds, s[c], b.invs);
+            v[c][1] = islook<1>(lds, s[(c + 3) & 3], b.invs);
+            v[c][2] = islook<2>(lds, s[(c + 2) & 3], b.invs);
+            v[c][3] = islook<3>(lds, s[(c + 1) & 3], b.invs);
+        } else {
+            // SubBytes + ShiftRows.  The S-box byte is taken from the T
+            // tables: T2 holds S(x) in byte 0, T3 in byte 1, T0 in byte 2 and
+            // T1 in byte 3.
+            v[c][0] = tlook<0>(lds, s[c], b.t[2]);
+            v[c][1] = tlook<1>(lds, s[(c + 1) & 3], b.t[3]);
+            v[c][2] = tlook<2>(lds, s[(c + 2) & 3], b.t[0]);
+            v[c][3] = tlook<3>(lds, s[(c + 3) & 3], b.t[1]);
+        }
+    }
+}
+
+// One middle round.
+template <bool kInv, int NB>
+__device__ __forceinline__ void mid_round(const uint32_t *lds, const Bases &b, uint32_t (&s)[NB][4],
                                           const uint32_t *k) {
-    uint32_t o[4];
+    uint32_t v[NB][4][4];
+    mid_lookups<kInv>(lds, b, s[0], v[0]);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int i1 = kInv ? (c + 3) & 3 : (c + 1) & 3;
-        const int i2 = (c + 2) & 3;
-        const int i3 = kInv ? (c + 1) & 3 : (c + 3) & 3;
-        o[c] = xor3(xor3(tlook<0>(lds, s[c], b.t[0]), tlook<1>(lds, s[i1], b.t[1]),
-                         tlook<2>(lds, s[i2], b.t[2])),
-                    tlook<3>(lds, s[i3], b.t[3]), k[c]);
+    for (int j = 0; j < NB; ++j) {
+        if (j + 1 < NB) mid_lookups<kInv>(lds, b, s[(j + 1) % NB], v[(j + 1) % NB]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            s[j][c] = xor3(xor3(v[j][c][0], v[j][c][1], v[j][c][2]), v[j][c][3], k[c]);
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) s[c] = o[c];
 }
 
-// Last forward round: SubBytes + ShiftRows + AddRoundKey.  The S-box byte is
-// taken from the T tables: T2 holds S(x) in byte 0, T3 in byte 1, T0 in byte
-// 2 and T1 in byte 3.
-__device__ __forceinline__ void last_round_fwd(const uint32_t *lds, const Bases &b,
-                                               uint32_t (&s)[4], const uint32_t *k) {
-    uint32_t o[4];
+// The last round (no MixColumns), with AddRoundKey.
+template <bool kInv, int NB>
+__device__ __forceinline__ void last_round(const uint32_t *lds, const Bases &b,
+                                           uint32_t (&s)[NB][4], const uint32_t *k) {
+    uint32_t v[NB][4][4];
+    last_lookups<kInv>(lds, b, s[0], v[0]);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        o[c] = merge4_xor(tlook<0>(lds, s[c], b.t[2]), tlook<1>(lds, s[(c + 1) & 3], b.t[3]),
-                          tlook<2>(lds, s[(c + 2) & 3], b.t[0]),
-                          tlook<3>(lds, s[(c + 3) & 3], b.t[1]), k[c]);
+    for (int j = 0; j < NB; ++j) {
+        if (j + 1 < NB) last_lookups<kInv>(lds, b, s[(j + 1) % NB], v[(j + 1) % NB]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            s[j][c] = kInv ? merge4_low_xor(v[j][c][0], v[j][c][1], v[j][c][2], v[j][c][3], k[c])
+                           : merge4_xor(v[j][c][0], v[j][c][1], v[j][c][2], v[j][c][3], k[c]);
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) s[c] = o[c];
-}
-
-// Last inverse round: InvSubBytes + InvShiftRows + AddRoundKey.
-__device__ __forceinline__ void last_round_inv(const uint32_t *lds, const Bases &b,
-                                               uint32_t (&s)[4], const uint32_t *k) {
-    uint32_t o[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        o[c] = merge4_low_xor(islook<0>(lds, s[c], b.invs),
-                              islook<1>(lds, s[(c + 3) & 3], b.invs),
-                              islook<2>(lds, s[(c + 2) & 3], b.invs),
-                              islook<3>(lds, s[(c + 1) & 3], b.invs), k[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) s[c] = o[c];
 }
 
 // Copies the table set into the LDS image; tid is the thread's index in the
@@ -132,22 +156,34 @@ __device__ __forceinline__ void last_round_inv(const uint32_t *lds, const Bases 
 // banks and the writes run at the LDS's 128 bytes per clock.  What bounds it
 // is then that rate: 128 KiB are 1024 clocks.
 template <bool kInv, int WG = kWG>
-__device__ __forceinline__ void stage_tables_tid(uint32_t *lds, const uint32_t *__restrict__ g,
-                                                 uint32_t tid) {
+struct TableWords {
+    uint32_t v[1024 / WG];
+    uint32_t s;   // inverse S-box word
+};
+
+template <bool kInv, int WG = kWG>
+__device__ __forceinline__ TableWords<kInv, WG> load_tables(const uint32_t *__restrict__ g,
+                                                            uint32_t tid) {
     static_assert(1024 % WG == 0 && WG % 256 == 0, "workgroup size");
     const uint32_t *src = g + (kInv ? kTd : kTe);
-    constexpr int kPer = 1024 / WG;
-    uint32_t v[kPer], w = 0;
+    TableWords<kInv, WG> w{};
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) v[k] = src[tid + uint32_t(k) * WG];
-    if constexpr (kInv) w = g[kInvSS + (tid & 255u)];
+    for (int k = 0; k < 1024 / WG; ++k) w.v[k] = src[tid + uint32_t(k) * WG];
+    if constexpr (kInv) w.s = g[kInvSS + (tid & 255u)];
+    return w;
+}
+
+template <bool kInv, int WG>
+__device__ __forceinline__ void write_tables(uint32_t *lds, const TableWords<kInv, WG> &w,
+                                             uint32_t tid) {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
+    for (int k = 0; k < 1024 / WG; ++k) {
         const uint32_t e = tid + uint32_t(k) * WG, t = e >> 8, x = e & 255u;
         uint32_t *row = lds + (t >> 1) * 16384u + x * 64u + (t & 1u) * 32u;
 #pragma unroll
         for (uint32_t i = 0; i < 8; ++i)
-            *reinterpret_cast<uint4 *>(row + 4u * ((i + tid) & 7u)) = make_uint4(v[k], v[k], v[k], v[k]);
+            *reinterpret_cast<uint4 *>(row + 4u * ((i + tid) & 7u)) =
+                make_uint4(w.v[k], w.v[k], w.v[k], w.v[k]);
     }
     if constexpr (kInv) {
         // The inverse S-box words: WG / 256 threads share an entry's copies.
@@ -156,14 +192,14 @@ __device__ __forceinline__ void stage_tables_tid(uint32_t *lds, const uint32_t *
 #pragma unroll
         for (uint32_t i = 0; i < kEach; ++i)
             *reinterpret_cast<uint4 *>(row + 4u * (((tid >> 8) * kEach + i + tid) & 7u)) =
-                make_uint4(w, w, w, w);
+                make_uint4(w.s, w.s, w.s, w.s);
     }
     __syncthreads();
 }
 
 template <bool kInv, int WG = kWG>
 __device__ __forceinline__ void stage_tables(uint32_t *lds, const uint32_t *__restrict__ g) {
-    stage_tables_tid<kInv, WG>(lds, g, threadIdx.x);
+    write_tables(lds, load_tables<kInv, WG>(g, threadIdx.x), threadIdx.x);
 }
 
 // The next share (or tile) for this wave: lane 0 adds one to the workgroup's count in

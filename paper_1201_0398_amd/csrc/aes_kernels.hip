@@ -210,8 +210,7 @@ __device__ __forceinline__ void rounds_v(const uint32_t *lds, const Bases &b, ui
         constexpr int kX = (R - 1) / 4, kI = 4 * ((R - 1) % 4);
         const uint32_t k[4] = {row_word<kI>(kq[kX]), row_word<kI + 1>(kq[kX]),
                                row_word<kI + 2>(kq[kX]), row_word<kI + 3>(kq[kX])};
-#pragma unroll
-        for (int j = 0; j < BPL; ++j) mid_round<kInv>(lds, b, s[j], k);
+        mid_round<kInv>(lds, b, s, k);
         rounds_v<kInv, BPL, R + 1, NR>(lds, b, s, kq);
     }
 }
@@ -236,7 +235,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
     // The workgroup's share count: the word after the forward tables, which
     // in decryption kernels is the first copy of InvS[0] (its high half is
     // zero after the staging; the InvS entry uses bytes 0 and 1).
-    __shared__ alignas(16) uint32_t lds[kInv ? kFwdWords + kInvSWords : kFwdWords + (kDyn ? 1 : 0)];
+    __shared__ uint32_t lds[kInv ? kFwdWords + kInvSWords : kFwdWords + (kDyn ? 1 : 0)];
     uint32_t *const count = lds + kFwdWords;
     // Odd waves issue at a higher priority than even ones (a workgroup's
     // waves go to the CU's four SIMDs in turn, so two SIMDs run high and two
@@ -459,19 +458,10 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
 #pragma unroll
         for (int r = 1; r < NR; ++r) {
             if (r < first) continue;
-            if constexpr (!kKeysV) {
-#pragma unroll
-                for (int j = 0; j < BPL; ++j) mid_round<kInv>(lds, b, s[j], &p.rk.w[4 * r]);
-            }
+            if constexpr (!kKeysV) mid_round<kInv>(lds, b, s, &p.rk.w[4 * r]);
         }
         if constexpr (kKeysV) rounds_v<kInv, BPL, (kCtr ? 3 : 1), NR>(lds, b, s, kq);
-#pragma unroll
-        for (int j = 0; j < BPL; ++j) {
-            if (kInv)
-                last_round_inv(lds, b, s[j], &p.rk.w[4 * NR]);
-            else
-                last_round_fwd(lds, b, s[j], &p.rk.w[4 * NR]);
-        }
+        last_round<kInv>(lds, b, s, &p.rk.w[4 * NR]);
         if constexpr (OP == Op::kCbcDec) {
             // Keeps the wave shuffles of the ciphertext below (DPP) after the
             // last round's table reads: placed among the rounds, they held 16
@@ -522,16 +512,16 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         // Partial last block: wave 0 of workgroup 0 computes its keystream
         // (the same block in every lane) and lane q < tail writes byte q.
         if (p.tail && blockIdx.x == 0 && threadIdx.x < 64) {
-            uint32_t s[4];
-            counter_state<OP>(p, p.n_full, s);
+            uint32_t s[1][4];
+            counter_state<OP>(p, p.n_full, s[0]);
 #pragma unroll
             for (int r = 1; r < NR; ++r) mid_round<false>(lds, b, s, &p.rk.w[4 * r]);
-            last_round_fwd(lds, b, s, &p.rk.w[4 * NR]);
+            last_round<false>(lds, b, s, &p.rk.w[4 * NR]);
             const uint32_t q = threadIdx.x;
             if (q < p.tail) {
                 const uint8_t *src = reinterpret_cast<const uint8_t *>(p.in + p.n_full);
                 uint8_t *dst = reinterpret_cast<uint8_t *>(p.out + p.n_full);
-                const uint32_t w = q < 4 ? s[0] : q < 8 ? s[1] : q < 12 ? s[2] : s[3];
+                const uint32_t w = q < 4 ? s[0][0] : q < 8 ? s[0][1] : q < 12 ? s[0][2] : s[0][3];
                 dst[q] = src[q] ^ uint8_t(w >> (8 * (q & 3)));
             }
         }
