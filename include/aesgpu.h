@@ -184,7 +184,7 @@ typedef struct {
 #define AESGPU_BATCH_NO_GRAPH 1u /* enqueue the launches directly, no hipGraph */
 
 /* Launch shape of a batch; zero fields take the defaults (4 blocks per lane,
- * and tiles of 256 to 8192 blocks, by the size of the batch).  tile_blocks must
+ * and tiles of 256 to 4096 blocks, by the size of the batch).  tile_blocks must
  * be a multiple of 64 * blocks_per_lane. */
 typedef struct {
     uint32_t blocks_per_lane; /* 1, 2 or 4 (decryption tiles run at 2 where it is 4) */
