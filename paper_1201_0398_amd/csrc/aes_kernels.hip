@@ -173,6 +173,52 @@ __device__ __forceinline__ uint32_t tab_u(const uint32_t *te, uint32_t t, uint32
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t w, int k) { return (w >> (8 * k)) & 0xFFu; }
 
+// What rounds 1 and 2 of CTR share over a wave's 64 * BPL counters, which start
+// at a multiple of 64 * BPL, so that they differ only in their low byte, and so
+// does the whitened counter block.  Round 1 (Eq. (1)): the varying byte feeds one
+// table term of output word 0; the other 15 terms and output words 1..3 are
+// wave-uniform.  Round 2: each output word has one term on word 0 (per block) and
+// three on words 1..3 (uniform).  The uniform lookups are scalar loads, once per
+// wave and tile.
+template <Op OP>
+struct CtrShare {
+    uint32_t c[4];   // round 2's uniform part, per output word
+    uint32_t word;   // the whitened varying word of the first counter
+};
+
+template <Op OP>
+__device__ __forceinline__ CtrShare<OP> ctr_share(const Params &p, uint32_t slot) {
+    CtrShare<OP> u{};
+    const uint32_t *te = p.tables + kTe;
+    uint32_t u1, u2, u3;        // round-1 output words 1..3
+    if constexpr (OP == Op::kCtrBe32) {
+        // Counter block: nonce words 0..2 (folded into cc.p by the host), word
+        // 3 = BE32(counter), whose byte 3 varies.
+        u.word = bswap32(p.ctr0 - p.voff + slot) ^ p.cc.kvar;
+        u1 = p.cc.p[1] ^ tab_u(te, 2, byte_of(u.word, 2));
+        u2 = p.cc.p[2] ^ tab_u(te, 1, byte_of(u.word, 1));
+        u3 = p.cc.p[3] ^ tab_u(te, 0, byte_of(u.word, 0));
+    } else {
+        // Counter block: the 128-bit LE integer whose words 1..3 are fixed over
+        // the launch (folded into cc.p by the host) and whose word 0 is ctr_y +
+        // slot; its byte 0 varies.
+        u.word = (p.ctr_y + slot) ^ p.cc.kvar;
+        u1 = p.cc.p[1] ^ tab_u(te, 3, byte_of(u.word, 3));
+        u2 = p.cc.p[2] ^ tab_u(te, 2, byte_of(u.word, 2));
+        u3 = p.cc.p[3] ^ tab_u(te, 1, byte_of(u.word, 1));
+    }
+    const uint32_t *k2 = &p.rk.w[8];
+    u.c[0] = tab_u(te, 1, byte_of(u1, 1)) ^ tab_u(te, 2, byte_of(u2, 2)) ^
+             tab_u(te, 3, byte_of(u3, 3)) ^ k2[0];
+    u.c[1] = tab_u(te, 0, byte_of(u1, 0)) ^ tab_u(te, 1, byte_of(u2, 1)) ^
+             tab_u(te, 2, byte_of(u3, 2)) ^ k2[1];
+    u.c[2] = tab_u(te, 0, byte_of(u2, 0)) ^ tab_u(te, 1, byte_of(u3, 1)) ^
+             tab_u(te, 3, byte_of(u1, 3)) ^ k2[2];
+    u.c[3] = tab_u(te, 0, byte_of(u3, 0)) ^ tab_u(te, 2, byte_of(u1, 2)) ^
+             tab_u(te, 3, byte_of(u2, 3)) ^ k2[3];
+    return u;
+}
+
 // Whitened counter block (round 0 done) of block idx for the CTR modes.
 template <Op OP>
 __device__ __forceinline__ void counter_state(const Params &p, uint64_t idx, uint32_t (&s)[4]) {
@@ -216,8 +262,8 @@ __device__ __forceinline__ void rounds_v(const uint32_t *lds, const Bases &b, ui
 }
 
 // kDyn: the waves claim the shares of the workgroup's tiles from a count in
-// LDS (launches with several tiles per CU); otherwise wave i computes share i
-// of each of the workgroup's tiles.
+// LDS (launches with several tiles per CU); otherwise the workgroup has one tile
+// and wave i computes its share i.
 template <Op OP, int NR, int BPL, bool kDyn>
 __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
     constexpr bool kInv = (OP == Op::kEcbDec || OP == Op::kCbcDec);
@@ -297,8 +343,18 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         if constexpr (!kInv)
             if (threadIdx.x == 0) *count = 0u;   // published by the staging barrier
     }
-    stage_tables<kInv>(lds, p.tables);
+    const TableWords<kInv> words = load_tables<kInv>(p.tables, threadIdx.x);
+    // With one share per wave, what a CTR share has in common is looked up while
+    // the tables are staged (two scalar loads one after the other, 0.5 us of a
+    // small call).
+    CtrShare<OP> ahead{};
+    if constexpr (kCtr && !kDyn) ahead = ctr_share<OP>(p, uint32_t(tile_of(cur)) + wave * (64u * BPL));
+    write_tables(lds, words, threadIdx.x);
     constexpr uint32_t kStep = kShareStep<kWM, BPL>;
+    // A CTR call's partial last block is the last wave's of workgroup 0: in a small
+    // call that wave has nothing else to do (the first wave, which did it after
+    // its share, made the call as long as two).
+    const bool tail_wave = kCtr && p.tail && blockIdx.x == 0 && wave == kWG / 64 - 1;
     uint32_t n_shares = 0;
     if constexpr (kDyn) {
         if (n_tiles_wg) {
@@ -309,7 +365,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
     } else {
         // A small tile leaves the workgroup's last waves without blocks: they
         // end here (the staging barrier was the last one).
-        if (wave * kStep >= p.tile) return;
+        if (wave * kStep >= p.tile && !tail_wave) return;
     }
     const Bases b = lane_bases();
     // AES-256, and AES-192 CTR and CBC, take their middle rounds' keys from
@@ -385,46 +441,15 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         if constexpr (OP == Op::kCbcDec)
             next_prev = load_wave_prev<BPL>(p.in, next_base, next_w, p.n_full, uint32_t(tile),
                                             kDyn ? p.prev_in : 0u);
-        // CTR rounds 1 and 2.  The wave's 64 * BPL counters start at a
-        // multiple of 64 * BPL, so they differ only in their low byte, and so
-        // does the whitened counter block.  Round 1 (Eq. (1)): the varying
-        // byte feeds one table term of output word 0; the other 15 terms and
-        // output words 1..3 are wave-uniform.  Round 2: each output word has
-        // one term on word 0 (per block) and three on words 1..3 (uniform).
-        // The uniform lookups are scalar loads, once per wave and tile.
-        uint32_t c[4] = {0, 0, 0, 0};   // round-2 uniform part, per output word
-        uint32_t y0 = 0;                // LE-128: counter word 0 of the wave's first slot
-        uint32_t w3u = 0;               // BE32: whitened word 3 of the wave's first counter
+        CtrShare<OP> u;
         if constexpr (kCtr) {
-            const uint32_t *te = p.tables + kTe;
-            uint32_t u1, u2, u3;        // round-1 output words 1..3
-            if constexpr (OP == Op::kCtrBe32) {
-                // Counter block: nonce words 0..2 (folded into cc.p by the
-                // host), word 3 = BE32(counter), whose byte 3 varies.
-                const uint32_t ctr_first = p.ctr0 - p.voff + uint32_t(base) + w * (64u * BPL);
-                w3u = bswap32(ctr_first) ^ p.cc.kvar;
-                u1 = p.cc.p[1] ^ tab_u(te, 2, byte_of(w3u, 2));
-                u2 = p.cc.p[2] ^ tab_u(te, 1, byte_of(w3u, 1));
-                u3 = p.cc.p[3] ^ tab_u(te, 0, byte_of(w3u, 0));
-            } else {
-                // Counter block: the 128-bit LE integer whose words 1..3 are
-                // fixed over the launch (folded into cc.p by the host) and
-                // whose word 0 is ctr_y + slot; its byte 0 varies.
-                y0 = p.ctr_y + uint32_t(base) + w * (64u * BPL);
-                const uint32_t s0u = y0 ^ p.cc.kvar;
-                u1 = p.cc.p[1] ^ tab_u(te, 3, byte_of(s0u, 3));
-                u2 = p.cc.p[2] ^ tab_u(te, 2, byte_of(s0u, 2));
-                u3 = p.cc.p[3] ^ tab_u(te, 1, byte_of(s0u, 1));
+            u = kDyn ? ctr_share<OP>(p, uint32_t(base) + w * (64u * BPL)) : ahead;
+            // (Opaque: the compiler would move the rounds out of the loop.)
+            if constexpr (!kDyn) {
+                asm volatile("" : "+v"(u.word));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(u.c[i]));
             }
-            const uint32_t *k2 = &p.rk.w[8];
-            c[0] = tab_u(te, 1, byte_of(u1, 1)) ^ tab_u(te, 2, byte_of(u2, 2)) ^
-                   tab_u(te, 3, byte_of(u3, 3)) ^ k2[0];
-            c[1] = tab_u(te, 0, byte_of(u1, 0)) ^ tab_u(te, 1, byte_of(u2, 1)) ^
-                   tab_u(te, 2, byte_of(u3, 2)) ^ k2[1];
-            c[2] = tab_u(te, 0, byte_of(u2, 0)) ^ tab_u(te, 1, byte_of(u3, 1)) ^
-                   tab_u(te, 3, byte_of(u1, 3)) ^ k2[2];
-            c[3] = tab_u(te, 0, byte_of(u3, 0)) ^ tab_u(te, 2, byte_of(u1, 2)) ^
-                   tab_u(te, 3, byte_of(u2, 3)) ^ k2[3];
         }
 #pragma unroll
         for (int j = 0; j < BPL; ++j) {
@@ -445,13 +470,13 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
                     // Slot j of lane L has counter ctr_first + 64 j + L, and
                     // ctr_first is a multiple of 64 * BPL > 64 j + L: the sum
                     // only sets low bits of the counter's low byte, which is
-                    // byte 3 of the big-endian word.
-                    low_byte_lookups(w3u ^ (low << 24), o);
+                    // byte 3 of the big-endian word (LE-128: byte 0).
+                    low_byte_lookups(u.word ^ (low << 24), o);
                 } else {
-                    low_byte_lookups((y0 | low) ^ p.cc.kvar, o);
+                    low_byte_lookups(u.word ^ low, o);
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) s[j][i] = o[i] ^ c[i];
+                for (int i = 0; i < 4; ++i) s[j][i] = o[i] ^ u.c[i];
             }
         }
         const int first = kCtr ? 3 : 1;
@@ -503,21 +528,23 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
             step(base, w, tile_of(cur), cur & 15u);
         }
     } else {
-        // A wave leaves the loop at the first tile that has no block for it.
-        for (uint64_t base = uint64_t(blockIdx.x) * tile; base + uint64_t(wave) * kStep < v_end;
+        // (At most one tile, for which `ahead` is; a loop, so that the compiler
+        // schedules the step as it does the other kernels'.)
+        const uint64_t end = wave * kStep < p.tile ? v_end : 0;
+        for (uint64_t base = uint64_t(blockIdx.x) * tile; base + uint64_t(wave) * kStep < end;
              base += stride)
             step(base, wave, base + stride, wave);
     }
     if constexpr (kCtr) {
-        // Partial last block: wave 0 of workgroup 0 computes its keystream
-        // (the same block in every lane) and lane q < tail writes byte q.
-        if (p.tail && blockIdx.x == 0 && threadIdx.x < 64) {
+        // Partial last block: its keystream (the same block in every lane), of
+        // which lane q < tail writes byte q.
+        if (tail_wave) {
             uint32_t s[1][4];
             counter_state<OP>(p, p.n_full, s[0]);
 #pragma unroll
             for (int r = 1; r < NR; ++r) mid_round<false>(lds, b, s, &p.rk.w[4 * r]);
             last_round<false>(lds, b, s, &p.rk.w[4 * NR]);
-            const uint32_t q = threadIdx.x;
+            const uint32_t q = threadIdx.x & 63u;
             if (q < p.tail) {
                 const uint8_t *src = reinterpret_cast<const uint8_t *>(p.in + p.n_full);
                 uint8_t *dst = reinterpret_cast<uint8_t *>(p.out + p.n_full);
