@@ -178,7 +178,7 @@ def launch_floor(torch) -> dict:
 
 
 def batched_bench(torch, A, ctx, rates: dict, reps: int, warm_s: float) -> dict:
-    """The 65,536-message batch (seed 3), encrypt direction, graph replays."""
+    """The 65,536-message batch (seed 3), encrypt direction."""
     import numpy as np
 
     from paper_1201_0398_amd import workloads
@@ -220,7 +220,7 @@ def batched_bench(torch, A, ctx, rates: dict, reps: int, warm_s: float) -> dict:
             "time_vs_single_buffer_aes128_ecb": round(sec / t_128, 3),
             "workload": "65,536 messages, log-uniform 16 B..1 MiB, own key each, key size "
                         "uniform over 128/192/256, ECB or CTR 50/50, encrypt, seed 3; one "
-                        "persistent launch with device key expansion, hipGraph replay"}
+                        "persistent launch with device key expansion"}
 
 
 def serving_bench(torch, A, ctx, n_requests: int, rates: dict | None = None, flags: int = 0,

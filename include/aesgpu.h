@@ -181,7 +181,7 @@ typedef struct {
     uint32_t ctr0;
 } aesgpu_msg;
 
-#define AESGPU_BATCH_NO_GRAPH 1u /* enqueue the launches directly, no hipGraph */
+#define AESGPU_BATCH_NO_GRAPH 1u /* launches without a hipGraph, which all are: no effect */
 
 /* Launch shape of a batch; zero fields take the defaults (4 blocks per lane,
  * and tiles of 256 to 4096 blocks, by the size of the batch).  tile_blocks must
@@ -229,13 +229,10 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
  * message whose input and output ranges meet is then EINVAL (each block
  * reads its predecessor's ciphertext); other overlap of d_in and d_out is
  * EINVAL.  Messages whose outputs overlap each other, or overlap a
- * CBC-decrypt message's input, give undefined output.  By
- * default the launches are captured once into a hipGraph and replayed; the
- * graph is re-captured when d_keys, d_in or d_out change.  On ROCm 7 a
- * replay costs 5-9 us more than launching the same kernels directly, which
- * matters only for small batches: plan those with AESGPU_BATCH_NO_GRAPH when
- * latency counts.  Calls on one plan must not overlap in time (they share
- * the plan's tile counters, which every run leaves at zero).
+ * CBC-decrypt message's input, give undefined output.  The
+ * launches (stats.launches of them) are enqueued directly: replaying them as a
+ * hipGraph took 5-9 us longer on ROCm 7.  Calls on one plan must not overlap in
+ * time (they share the plan's tile counters, which every run leaves at zero).
  * Errors: EINVAL, EALIGN, EHIP.
  */
 int aesgpu_batch_run(aesgpu_batch *plan, const uint8_t *d_keys, size_t n_key_slots,
@@ -247,7 +244,7 @@ int aesgpu_batch_run(aesgpu_batch *plan, const uint8_t *d_keys, size_t n_key_slo
  * harnesses that forbid hipMalloc): plans and runs one batch in a single call
  * and allocates no device memory.  Messages, keys, buffers, stream and cfg
  * mean what they mean for aesgpu_batch_plan() and aesgpu_batch_run(), with the
- * same errors; the launches are enqueued directly (no hipGraph).  The batch's
+ * same errors.  The batch's
  * device descriptors (64 bytes per message, 16 per tile, the queue counters
  * and the CBC-encryption groups) go to a fixed scratch area of
  * AESGPU_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until
@@ -269,7 +266,7 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
 /* Plan statistics (host only).  Errors: EINVAL. */
 int aesgpu_batch_info(const aesgpu_batch *plan, aesgpu_batch_stats *out);
 
-/* Frees the plan (device descriptors, graph).  NULL is ignored.  The caller
+/* Frees the plan (its device descriptors).  NULL is ignored.  The caller
  * must make sure no run of the plan is still executing. */
 void aesgpu_batch_free(aesgpu_batch *plan);
 

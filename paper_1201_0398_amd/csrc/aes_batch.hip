@@ -24,13 +24,15 @@
 //   the middle rounds run as one straight sequence shared by the three key
 //   sizes, their round keys given to every lane by DPP row broadcasts.  CTR
 //   tiles precompute their round-1 constants.
-// * The persistent launches are captured once into a hipGraph and replayed
-//   (the kernel leaves its queue counters at zero); the graph is re-captured
-//   when the buffers change.
+// * A run is one kernel launch, or two with CBC encryption (the batch kernel
+//   leaves its queue counters at zero).  On ROCm 7 replaying them as a hipGraph
+//   took 5 to 9 us longer than launching them, at every size, and new buffers
+//   needed a new graph, so there is none.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -344,48 +346,48 @@ __device__ __forceinline__ void crypt_step(const uint32_t *lds, const Bases &b, 
                                            const uint4 (&prev)[NB], rsrc_t rout) {
     uint32_t s[NB][4];
     uint32_t rk[4];
-            round_key(kreg, 0, rk);
+    round_key(kreg, 0, rk);
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const uint64_t idx = base + uint64_t(j) * 64u + lane;
-                if (ctr) {
-                    counter_round1(lds, b, cc, m.ctr0 + uint32_t(idx), s[j]);
-                } else {
-                    s[j][0] = d[j].x ^ rk[0];
-                    s[j][1] = d[j].y ^ rk[1];
-                    s[j][2] = d[j].z ^ rk[2];
-                    s[j][3] = d[j].w ^ rk[3];
-                }
-            }
-            if (!ctr) {
-                round_key(kreg, 1, rk);
-                mid_round<kInv>(lds, b, s, rk);
-            }
-            if constexpr (NB > 1) {
-                // Rounds 2 .. nr - 1 as one straight sequence of 12 rounds that
-                // AES-192 enters at its third round and AES-128 at its fifth (round
-                // q + nr - 13 at position q), in chunks of two or four rounds whose
-                // round keys come from the per-tile key registers by row broadcast.
-                // Unlike a rolled loop, or round keys read into SGPRs round by round,
-                // this lets the compiler overlap more of the rounds' table reads.
-                switch (nr) {
-                    case 14:
-                        mid_round_chunk<kInv, NB, 1, 2>(lds, b, kq, s);
-                        [[fallthrough]];
-                    case 12:
-                        mid_round_chunk<kInv, NB, 3, 2>(lds, b, kq, s);
-                        [[fallthrough]];
-                    default:
-                        mid_round_chunk<kInv, NB, 5, 4>(lds, b, kq, s);
-                        mid_round_chunk<kInv, NB, 9, 4>(lds, b, kq, s);
-                }
-            } else {
+    for (int j = 0; j < NB; ++j) {
+        const uint64_t idx = base + uint64_t(j) * 64u + lane;
+        if (ctr) {
+            counter_round1(lds, b, cc, m.ctr0 + uint32_t(idx), s[j]);
+        } else {
+            s[j][0] = d[j].x ^ rk[0];
+            s[j][1] = d[j].y ^ rk[1];
+            s[j][2] = d[j].z ^ rk[2];
+            s[j][3] = d[j].w ^ rk[3];
+        }
+    }
+    if (!ctr) {
+        round_key(kreg, 1, rk);
+        mid_round<kInv>(lds, b, s, rk);
+    }
+    if constexpr (NB > 1) {
+        // Rounds 2 .. nr - 1 as one straight sequence of 12 rounds that
+        // AES-192 enters at its third round and AES-128 at its fifth (round
+        // q + nr - 13 at position q), in chunks of two or four rounds whose
+        // round keys come from the per-tile key registers by row broadcast.
+        // Unlike a rolled loop, or round keys read into SGPRs round by round,
+        // this lets the compiler overlap more of the rounds' table reads.
+        switch (nr) {
+            case 14:
+                mid_round_chunk<kInv, NB, 1, 2>(lds, b, kq, s);
+                [[fallthrough]];
+            case 12:
+                mid_round_chunk<kInv, NB, 3, 2>(lds, b, kq, s);
+                [[fallthrough]];
+            default:
+                mid_round_chunk<kInv, NB, 5, 4>(lds, b, kq, s);
+                mid_round_chunk<kInv, NB, 9, 4>(lds, b, kq, s);
+        }
+    } else {
 #pragma unroll 1
-                for (uint32_t r = 2; r < nr; ++r) {
-                    round_key(kreg, r, rk);
-                    mid_round<kInv>(lds, b, s, rk);
-                }
-            }
+        for (uint32_t r = 2; r < nr; ++r) {
+            round_key(kreg, r, rk);
+            mid_round<kInv>(lds, b, s, rk);
+        }
+    }
     round_key(kreg, nr, rk);
     last_round<kInv>(lds, b, s, rk);
 #pragma unroll
@@ -1563,7 +1565,6 @@ struct aesgpu_batch {
     aesgpu_ctx *ctx = nullptr;
     uint32_t bpl = kDefaultBpl;
     uint32_t tile_blocks = kDefaultTileBlocks;
-    bool use_graph = true;
     size_t n_msgs = 0;
     size_t n_tiles[2] = {0, 0};    // forward, inverse
     BatchTotals tot;
@@ -1575,11 +1576,6 @@ struct aesgpu_batch {
     uint32_t *d_cbc_list = nullptr;
     uint4 *d_cbc_dummy = nullptr;
     size_t n_cbc_groups = 0;
-    hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    const void *cap_keys = nullptr, *cap_in = nullptr;
-    void *cap_out = nullptr;
 };
 
 namespace {
@@ -1602,26 +1598,16 @@ int check_run(const BatchTotals &tot, const uint8_t *d_keys, size_t n_key_slots,
 
 // The launch shape a config asks for (NULL: the defaults; tile_blocks 0: the
 // library's choice).
-int batch_shape(const aesgpu_batch_config *cfg, uint32_t &bpl, uint32_t &tile_blocks,
-                bool &use_graph) {
+int batch_shape(const aesgpu_batch_config *cfg, uint32_t &bpl, uint32_t &tile_blocks) {
     bpl = kDefaultBpl;
     tile_blocks = 0;
-    use_graph = true;
     if (cfg) {
         if (cfg->blocks_per_lane) bpl = cfg->blocks_per_lane;
         tile_blocks = cfg->tile_blocks;
-        use_graph = !(cfg->flags & AESGPU_BATCH_NO_GRAPH);
     }
     if (bpl != 1 && bpl != 2 && bpl != 4) return AESGPU_EINVAL;
     if (tile_blocks % (64u * bpl) != 0 || tile_blocks > (1u << 24)) return AESGPU_EINVAL;
     return AESGPU_OK;
-}
-
-void release_graph(aesgpu_batch *b) {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
 }
 
 int enqueue(aesgpu_batch *b, const uint8_t *keys, const void *in, void *out, hipStream_t s) {
@@ -1658,8 +1644,7 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     if (!ctx || (m > 0 && !msgs)) return AESGPU_EINVAL;
     if (m > 0xFFFFFFFFull) return AESGPU_EINVAL;
     uint32_t bpl, tile_blocks;
-    bool use_graph;
-    const int shape = batch_shape(cfg, bpl, tile_blocks, use_graph);
+    const int shape = batch_shape(cfg, bpl, tile_blocks);
     if (shape != AESGPU_OK) return shape;
     if (!tile_blocks) tile_blocks = default_tile_blocks(ctx, msgs, m);
 
@@ -1679,7 +1664,6 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     b->ctx = ctx;
     b->bpl = bpl;
     b->tile_blocks = tile_blocks;
-    b->use_graph = use_graph;
     b->n_msgs = m;
     b->n_tiles[0] = tiles[0].size();
     b->n_tiles[1] = tiles[1].size();
@@ -1710,22 +1694,23 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     b->d_cbc_dummy = reinterpret_cast<uint4 *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg);
     b->d_cbc_list =
         reinterpret_cast<uint32_t *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg + dummy);
-    bool ok = true;
-    if (cg)
-        ok &= hipMemcpy(b->d_cbc_groups, cbc_groups.data(), cg, hipMemcpyHostToDevice) ==
-              hipSuccess;
-    if (!cbc_list.empty())
-        ok &= hipMemcpy(b->d_cbc_list, cbc_list.data(), cbc_list.size() * sizeof(uint32_t),
-                        hipMemcpyHostToDevice) == hipSuccess;
-    if (msg_bytes) ok &= hipMemcpy(b->d_msgs, dm.data(), msg_bytes, hipMemcpyHostToDevice) == hipSuccess;
-    if (t0) ok &= hipMemcpy(b->d_tiles[0], tiles[0].data(), t0, hipMemcpyHostToDevice) == hipSuccess;
-    if (t1) ok &= hipMemcpy(b->d_tiles[1], tiles[1].data(), t1, hipMemcpyHostToDevice) == hipSuccess;
-    // The queue counters start at zero once; every launch leaves them zero.
-    const std::vector<uint8_t> zeros(kCounterBytes, 0);
-    ok &= hipMemcpy(b->d_counters, zeros.data(), kCounterBytes, hipMemcpyHostToDevice) ==
-          hipSuccess;
-    ok &= hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) == hipSuccess;
-    if (!ok) {
+    // One upload for all of it: a copy from pageable memory takes about 10 us
+    // whatever its size.  The queue counters start at zero once; every launch
+    // leaves them zero.
+    const std::unique_ptr<char[]> image(new (std::nothrow) char[bytes]());
+    if (!image) {
+        aesgpu_batch_free(b);
+        return AESGPU_ENOMEM;
+    }
+    auto put = [&](const void *to, const void *from, size_t n) {
+        if (n) std::memcpy(image.get() + (static_cast<const char *>(to) - base), from, n);
+    };
+    put(b->d_msgs, dm.data(), msg_bytes);
+    put(b->d_tiles[0], tiles[0].data(), t0);
+    put(b->d_tiles[1], tiles[1].data(), t1);
+    put(b->d_cbc_groups, cbc_groups.data(), cg);
+    put(b->d_cbc_list, cbc_list.data(), cl);
+    if (hipMemcpy(b->d_mem, image.get(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
         aesgpu_batch_free(b);
         return AESGPU_EHIP;
     }
@@ -1742,28 +1727,7 @@ int aesgpu_batch_run(aesgpu_batch *b, const uint8_t *d_keys, size_t n_key_slots,
     DeviceGuard g(b->ctx->device);
     if (!g.ok()) return AESGPU_EHIP;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (!b->use_graph) return enqueue(b, d_keys, d_in, d_out, s);
-    if (!b->exec || b->cap_keys != d_keys || b->cap_in != d_in || b->cap_out != d_out) {
-        release_graph(b);
-        if (hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
-            return AESGPU_EHIP;
-        const int st = enqueue(b, d_keys, d_in, d_out, b->cap_stream);
-        hipGraph_t graph = nullptr;
-        const hipError_t e = hipStreamEndCapture(b->cap_stream, &graph);
-        if (st != AESGPU_OK || e != hipSuccess || !graph) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return AESGPU_EHIP;
-        }
-        b->graph = graph;
-        if (hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-            release_graph(b);
-            return AESGPU_EHIP;
-        }
-        b->cap_keys = d_keys;
-        b->cap_in = d_in;
-        b->cap_out = d_out;
-    }
-    return hipGraphLaunch(b->exec, s) == hipSuccess ? AESGPU_OK : AESGPU_EHIP;
+    return enqueue(b, d_keys, d_in, d_out, s);
 }
 
 int aesgpu_batch_info(const aesgpu_batch *b, aesgpu_batch_stats *out) {
@@ -1784,8 +1748,6 @@ void aesgpu_batch_free(aesgpu_batch *b) {
     if (!b) return;
     {
         DeviceGuard g(b->ctx->device);
-        release_graph(b);
-        if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
         if (b->d_mem) (void)hipFree(b->d_mem);
     }
     delete b;
@@ -1798,8 +1760,7 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     if (!ctx || (m > 0 && !msgs)) return AESGPU_EINVAL;
     if (m > 0xFFFFFFFFull) return AESGPU_EINVAL;
     uint32_t bpl, tile_blocks;
-    bool use_graph;
-    const int shape = batch_shape(cfg, bpl, tile_blocks, use_graph);
+    const int shape = batch_shape(cfg, bpl, tile_blocks);
     if (shape != AESGPU_OK) return shape;
     // Host-side planning reuses this thread's buffers from call to call.
     thread_local std::vector<DevMsg> dm;
@@ -1874,7 +1835,6 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     L.n_cu = ctx->n_cu;
     L.bpl = bpl;
     set_totals(L, tot);
-    (void)use_graph;
     return enqueue_batch(L, s);
 }
 
