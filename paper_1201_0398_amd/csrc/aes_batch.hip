@@ -233,25 +233,6 @@ __device__ __forceinline__ void counter_round1(const uint32_t *lds, const Bases 
     s[3] = cc.p[3] ^ tlook<0>(lds, w3, b.t[0]);
 }
 
-// Block loads and stores of a tile with a cache policy: 0 (the default) for
-// launches, whose start and end make memory coherent; kCoherent for the
-// resident kernel, whose tiles must see inputs and publish outputs
-// device-wide without L2 invalidations or write-backs (sc1: agent-coherent
-// accesses).
-constexpr int kCoherent = 16;
-
-template <int kPolicy>
-__device__ __forceinline__ uint4 tile_load16(rsrc_t r, uint32_t offset) {
-    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, kPolicy);
-    return make_uint4(x[0], x[1], x[2], x[3]);
-}
-
-template <int kPolicy>
-__device__ __forceinline__ void tile_store16(rsrc_t r, uint32_t offset, const uint4 &v) {
-    const u32x4 x = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(x, r, offset, 0, kPolicy);
-}
-
 // k[i] = lane I0 + i of x's row, in every lane (DPP row broadcast).
 template <int I0, int N, int... Is>
 __device__ __forceinline__ void row_words(uint32_t x, uint32_t (&k)[N],
@@ -418,7 +399,7 @@ __device__ __forceinline__ void crypt_step(const uint32_t *lds, const Bases &b, 
                 o.w ^= prev[j].w & cbc_mask;
             }
         }
-        tile_store16<kPolicy>(rout, (step_off + uint32_t(j) * 64u + lane) * 16u, o);
+        buffer_store16<kPolicy>(rout, (step_off + uint32_t(j) * 64u + lane) * 16u, o);
     }
 }
 
@@ -451,7 +432,7 @@ __device__ __forceinline__ uint32_t load_key(const BatchParams &p, uint32_t slot
 // key is expanded, an expansion of about 1 us and the descriptors fetched ahead
 // took 65,536 messages of up to 16 KiB from 225 to 210 us, and 8 of 4 KiB
 // from 11.6 to 11.0 us.
-template <bool kInv, int BPL, int kPolicy = 0, class F, class G>
+template <bool kInv, int BPL, int kPolicy, class F, class G>
 __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, const BatchParams &p,
                                          const DevMsg &m, const Tile &tile, uint32_t key,
                                          F &&after_key, G &&before_steps) {
@@ -508,16 +489,16 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
     uint4 next[BPL], next_prev[BPL];
     uint4 gd = make_uint4(0, 0, 0, 0), gp = make_uint4(0, 0, 0, 0);
     if constexpr (BPL > 1) {
-        gd = tile_load16<kPolicy>(rin_all, (g + lane) * 16u);
-        if constexpr (kInv) gp = tile_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
+        gd = buffer_load16<kPolicy>(rin_all, (g + lane) * 16u);
+        if constexpr (kInv) gp = buffer_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
     }
 #pragma unroll
     for (int j = 0; j < BPL; ++j)
-        next[j] = tile_load16<kPolicy>(rin, (h0 + uint32_t(j) * 64u + lane) * 16u);
+        next[j] = buffer_load16<kPolicy>(rin, (h0 + uint32_t(j) * 64u + lane) * 16u);
     if constexpr (kInv) {
 #pragma unroll
         for (int j = 0; j < BPL; ++j)
-            next_prev[j] = tile_load16<kPolicy>(rprev, (h0 + uint32_t(j) * 64u + lane - pshift) * 16u);
+            next_prev[j] = buffer_load16<kPolicy>(rprev, (h0 + uint32_t(j) * 64u + lane - pshift) * 16u);
     }
 
     // (The resident kernel has schedules only.)
@@ -572,8 +553,8 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
                 g = h1;
                 stop = n_blk;
             }
-            gd = tile_load16<kPolicy>(rin_all, (g + lane) * 16u);
-            if constexpr (kInv) gp = tile_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
+            gd = buffer_load16<kPolicy>(rin_all, (g + lane) * 16u);
+            if constexpr (kInv) gp = buffer_load16<kPolicy>(rprev_all, (g + lane - pshift) * 16u);
             crypt_step<kInv, 1, kPolicy>(lds, b, kreg, kq, nr, ctr, cc, m, cbc_mask,
                                          first + now, now, lane, d, prev, rout_g);
         }
@@ -622,7 +603,7 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
                 uint4 d[BPL];
 #pragma unroll
                 for (int j = 0; j < BPL; ++j) {
-                    d[j] = tile_load16<kPolicy>(rin_all, (step_off + uint32_t(j) * 64u + lane) * 16u);
+                    d[j] = buffer_load16<kPolicy>(rin_all, (step_off + uint32_t(j) * 64u + lane) * 16u);
                     if constexpr (!kKept)
                         low_byte_lookups(
                             lds, b, cc,
@@ -648,7 +629,7 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
                 last_round<false>(lds, b, s, rk);
 #pragma unroll
                 for (int j = 0; j < BPL; ++j)
-                    tile_store16<kPolicy>(rout, (step_off + uint32_t(j) * 64u + lane) * 16u,
+                    buffer_store16<kPolicy>(rout, (step_off + uint32_t(j) * 64u + lane) * 16u,
                                           make_uint4(s[j][0] ^ d[j].x, s[j][1] ^ d[j].y,
                                                      s[j][2] ^ d[j].z, s[j][3] ^ d[j].w));
             }
@@ -669,7 +650,7 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
         const rsrc_t none = buffer_rsrc(out, 0);
 #pragma unroll
         for (int j = 0; j < BPL; ++j)
-            tile_store16<kPolicy>(none, (uint32_t(j) * 64u + lane) * 16u, make_uint4(0, 0, 0, 0));
+            buffer_store16<kPolicy>(none, (uint32_t(j) * 64u + lane) * 16u, make_uint4(0, 0, 0, 0));
     }
     for (uint32_t step_off = h0; step_off < h1; step_off += kStep) {
         // Keep the round-key reads inside the loop: hoisting all of them would
@@ -679,13 +660,13 @@ __device__ __forceinline__ void run_tile(const uint32_t *lds, const Bases &b, co
 #pragma unroll
         for (int j = 0; j < BPL; ++j) {
             d[j] = next[j];
-            next[j] = tile_load16<kPolicy>(rin, (step_off + kStep + uint32_t(j) * 64u + lane) * 16u);
+            next[j] = buffer_load16<kPolicy>(rin, (step_off + kStep + uint32_t(j) * 64u + lane) * 16u);
         }
         if constexpr (kInv) {
 #pragma unroll
             for (int j = 0; j < BPL; ++j) {
                 prev[j] = next_prev[j];
-                next_prev[j] = tile_load16<kPolicy>(
+                next_prev[j] = buffer_load16<kPolicy>(
                     rprev, (step_off + kStep + uint32_t(j) * 64u + lane - pshift) * 16u);
             }
         }
@@ -982,7 +963,7 @@ __device__ __forceinline__ void drain_queue(uint32_t *lds, const Bases &b, uint3
         listed = at < p.n_static[set];
         const uint32_t vt = load_words(p.tiles[set] + (listed ? at : 0u));
         uint32_t vm = 0, vk = 0;
-        run_tile<kInv, BPL>(
+        run_tile<kInv, BPL, kCached>(
             lds, b, p, w.m, w.tile, w.key,
             [&] { vm = load_words(p.msgs + __builtin_amdgcn_readlane(vt, 0)); },
             [&] {

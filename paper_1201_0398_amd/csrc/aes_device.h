@@ -243,14 +243,25 @@ __device__ __forceinline__ rsrc_t buffer_rsrc(const void *base, uint32_t bytes) 
                                              kRawBufferWord3);
 }
 
+// Their cache policy: kCached (the default) where what is written may be read
+// again from the caches; kStreamed (nt) for buffers too large for that;
+// kCoherent (sc1, agent-coherent) for a kernel that runs while others produce
+// its inputs and use its outputs, and must see and publish them device-wide
+// without L2 invalidations or write-backs.
+constexpr int kCached = 0;
+constexpr int kStreamed = 2;
+constexpr int kCoherent = 16;
+
+template <int kPolicy>
 __device__ __forceinline__ uint4 buffer_load16(rsrc_t r, uint32_t offset) {
-    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, 0);
+    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, kPolicy);
     return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
+template <int kPolicy>
 __device__ __forceinline__ void buffer_store16(rsrc_t r, uint32_t offset, const uint4 &v) {
     const u32x4 x = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(x, r, offset, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, offset, 0, kPolicy);
 }
 
 // Pointers into the constant address space: a load through one with a

@@ -113,15 +113,27 @@ __device__ __forceinline__ uint32_t lane_offset(const TileView &v, int j) {
     return (tile_slot<kWaveMajor, BPL>(v.w, j) - v.shift) * 16u;
 }
 
+// Kernels of 2 and 4 blocks per lane run on 128 MiB and more, input and output
+// as large as the 256 MB Infinity Cache together: they stream past the caches.
+// Measured (µs, cached / streamed, three pairs of buffers in turn): AES-128 ECB
+// encryption 128 MiB 92.2 / 88.8, 190 MiB 132.8 / 129.5, 256 MiB 176.0 / 172.7,
+// 1 GiB 680.8 / 675.6; CTR 1 GiB 586 / 575; with a copy of the output behind it
+// 128 MiB 145 / 129, 190 MiB 199 / 195, 1 GiB 1022 / 1021.  Streaming smaller
+// calls makes them faster too (64 MiB 45.6 / 42.3 with streamed stores), but
+// whoever reads their output next pays more than that (61.6 / 65.4).
+template <int BPL>
+constexpr int kBlockPolicy = BPL > 1 ? kStreamed : kCached;
+
 template <bool kWaveMajor, int BPL>
 __device__ __forceinline__ void load_tile(uint4 (&v)[BPL], const TileView &t) {
 #pragma unroll
-    for (int j = 0; j < BPL; ++j) v[j] = buffer_load16(t.in, lane_offset<kWaveMajor, BPL>(t, j));
+    for (int j = 0; j < BPL; ++j)
+        v[j] = buffer_load16<kBlockPolicy<BPL>>(t.in, lane_offset<kWaveMajor, BPL>(t, j));
 }
 
 template <bool kWaveMajor, int BPL>
 __device__ __forceinline__ void store_block(const TileView &t, int j, const uint4 &o) {
-    buffer_store16(t.out, lane_offset<kWaveMajor, BPL>(t, j), o);
+    buffer_store16<kBlockPolicy<BPL>>(t.out, lane_offset<kWaveMajor, BPL>(t, j), o);
 }
 
 // Lane L gets x of lane L - 1 (a DPP shift of the wave); lane 0 keeps lane0.
@@ -162,7 +174,7 @@ __device__ __forceinline__ uint4 load_wave_prev(const uint4 *in, uint64_t base, 
                           (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(at >> 32)))) << 32);
     const rsrc_t r = buffer_rsrc(reinterpret_cast<const void *>(at_u),
                                  uint32_t(__builtin_amdgcn_readfirstlane(bytes)));
-    return buffer_load16(r, (w * 64u * BPL - shift) * 16u);
+    return buffer_load16<kCached>(r, (w * 64u * BPL - shift) * 16u);
 }
 
 // T_t[x] from the table copy in device memory, for an index that is the same
@@ -398,7 +410,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         const rsrc_t none = buffer_rsrc(p.out, 0);
 #pragma unroll
         for (int j = 0; j < BPL; ++j)
-            buffer_store16(none, lane_offset<kWM, BPL>(view, j), make_uint4(0, 0, 0, 0));
+            buffer_store16<kCached>(none, lane_offset<kWM, BPL>(view, j), make_uint4(0, 0, 0, 0));
     }
     // Round-1 word 0 of a CTR block whose whitened varying word is `w`, and the
     // four round-2 lookups on it.
