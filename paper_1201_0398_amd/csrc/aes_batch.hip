@@ -1386,6 +1386,32 @@ int launch_resident(const ResidentLaunch &L, hipStream_t s) {
                                                                                  : AESGPU_EHIP;
 }
 
+namespace {
+
+// Stable, longest tile first.  Many tiles are dealt out by their length, 12 bits
+// at a time (lengths are 1 .. tile_blocks <= 2^24): with 147,071 tiles of up to
+// 4096 blocks build_tiles() took 3.0 ms, 5.7 with a comparison sort, with
+// 9,436 tiles 125 us and 276.  The comparison sort stays for a few tiles, for
+// which clearing the counts (32 KiB) would be most of the work.
+void sort_longest_first(std::vector<Tile> &t, uint32_t tile_blocks) {
+    if (t.size() < 1024) {
+        std::stable_sort(t.begin(), t.end(),
+                         [](const Tile &a, const Tile &b) { return a.n_blocks > b.n_blocks; });
+        return;
+    }
+    std::vector<Tile> to(t.size());
+    for (uint32_t shift = 0; shift == 0 || (tile_blocks - 1) >> shift; shift += 12) {
+        auto digit = [&](const Tile &x) { return ((tile_blocks - x.n_blocks) >> shift) & 4095u; };
+        std::vector<size_t> at(4097, 0);
+        for (const Tile &x : t) ++at[digit(x) + 1];
+        for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+        for (const Tile &x : t) to[at[digit(x)]++] = x;
+        t.swap(to);
+    }
+}
+
+}  // namespace
+
 int build_tiles(const aesgpu_msg *msgs, size_t m, uint32_t tile_blocks, std::vector<DevMsg> &dm,
                 std::vector<Tile> (&tiles)[2], std::vector<uint32_t> &cbc_list,
                 std::vector<Tile> &cbc_groups, BatchTotals &tot) {
@@ -1455,9 +1481,7 @@ int build_tiles(const aesgpu_msg *msgs, size_t m, uint32_t tile_blocks, std::vec
             f += n;
         }
     }
-    for (auto &t : tiles)
-        std::stable_sort(t.begin(), t.end(),
-                         [](const Tile &a, const Tile &b) { return a.n_blocks > b.n_blocks; });
+    for (auto &t : tiles) sort_longest_first(t, tile_blocks);
     for (int q = 0; q < 2; ++q) {
         uint64_t left = tot.blocks[q] / 8;
         size_t i = tiles[q].size();
@@ -1675,23 +1699,39 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     b->d_cbc_dummy = reinterpret_cast<uint4 *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg);
     b->d_cbc_list =
         reinterpret_cast<uint32_t *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg + dummy);
-    // One upload for all of it: a copy from pageable memory takes about 10 us
-    // whatever its size.  The queue counters start at zero once; every launch
-    // leaves them zero.
-    const std::unique_ptr<char[]> image(new (std::nothrow) char[bytes]());
-    if (!image) {
-        aesgpu_batch_free(b);
-        return AESGPU_ENOMEM;
-    }
-    auto put = [&](const void *to, const void *from, size_t n) {
-        if (n) std::memcpy(image.get() + (static_cast<const char *>(to) - base), from, n);
+    // The queue counters start at zero once; every launch leaves them zero.
+    // A copy from pageable memory takes about 10 us whatever its size: a small
+    // plan is put together on the host and goes up in one (256 messages: 80 us,
+    // about 100 of them saved).  A large one goes up part by part: putting
+    // together the 6.5 MB of 65,536 messages costs 0.5 to 1 ms.
+    struct Part {
+        void *to;
+        const void *from;
+        size_t n;
     };
-    put(b->d_msgs, dm.data(), msg_bytes);
-    put(b->d_tiles[0], tiles[0].data(), t0);
-    put(b->d_tiles[1], tiles[1].data(), t1);
-    put(b->d_cbc_groups, cbc_groups.data(), cg);
-    put(b->d_cbc_list, cbc_list.data(), cl);
-    if (hipMemcpy(b->d_mem, image.get(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    constexpr size_t kOneUploadBytes = size_t(256) << 10;
+    static const char zero[kCounterBytes] = {};
+    const Part parts[] = {{b->d_msgs, dm.data(), msg_bytes},
+                          {b->d_tiles[0], tiles[0].data(), t0},
+                          {b->d_tiles[1], tiles[1].data(), t1},
+                          {b->d_counters, zero, kCounterBytes},
+                          {b->d_cbc_groups, cbc_groups.data(), cg},
+                          {b->d_cbc_list, cbc_list.data(), cl}};
+    bool ok = true;
+    if (bytes <= kOneUploadBytes) {
+        const std::unique_ptr<char[]> image(new (std::nothrow) char[bytes]());
+        if (!image) {
+            aesgpu_batch_free(b);
+            return AESGPU_ENOMEM;
+        }
+        for (const Part &p : parts)
+            if (p.n) std::memcpy(image.get() + (static_cast<char *>(p.to) - base), p.from, p.n);
+        ok = hipMemcpy(b->d_mem, image.get(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+    } else {
+        for (const Part &p : parts)
+            ok = ok && (!p.n || hipMemcpy(p.to, p.from, p.n, hipMemcpyHostToDevice) == hipSuccess);
+    }
+    if (!ok) {
         aesgpu_batch_free(b);
         return AESGPU_EHIP;
     }
