@@ -1105,6 +1105,7 @@ __global__ __launch_bounds__(kWG) void batch_kernel(BatchParams p) {
 // launch starts there.
 
 constexpr uint64_t kNoTile = ~0ull;
+constexpr uint32_t kShortTile = 512;   // blocks
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v));
@@ -1227,6 +1228,15 @@ __device__ void serve_ring(const uint32_t *lds, const Bases &b, const ResidentLa
             // producer left it and its output is visible device-wide once the
             // stores are complete, with no L2 invalidation or write-back (a
             // fence at this scope costs one per tile, and those serialise).
+            // Short tiles (small requests, whose latency they are) issue before long
+            // ones, and both before waves that poll.  p50 / p99 at 340 k req/s 70 / 642 us -> 64 / 637, at
+            // 170 k 56 / 334 -> 54 / 331; saturation the same.  With long tiles at
+            // the pollers' priority p50 fell to 62 and p99 rose to 649; with one
+            // priority for all tiles neither moved.
+            if (r.n_blocks <= kShortTile)
+                __builtin_amdgcn_s_setprio(3);
+            else
+                __builtin_amdgcn_s_setprio(1);
             run_tile<kInv, BPL, kCoherent>(lds, b, bp, m, tile,
                                            load_schedule<kInv>(p.sched, m.key_slot, m.nr),
                                            [] {}, [] {});
@@ -1234,6 +1244,7 @@ __device__ void serve_ring(const uint32_t *lds, const Bases &b, const ResidentLa
             // counter only grows (modulo 2^32); the record holds the count at
             // which this request is complete, and the wave that reaches it
             // reports the request to the host, which reads no output data.
+            __builtin_amdgcn_s_setprio(0);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane == 0) {
                 const uint32_t n = __hip_atomic_fetch_add(p.tiles_done + r.req_slot, 1u,
