@@ -293,7 +293,8 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
     // The workgroup's share count: the word after the forward tables, which
     // in decryption kernels is the first copy of InvS[0] (its high half is
     // zero after the staging; the InvS entry uses bytes 0 and 1).
-    __shared__ uint32_t lds[kInv ? kFwdWords + kInvSWords : kFwdWords + (kDyn ? 1 : 0)];
+    constexpr uint32_t kLdsWords = kInv ? kFwdWords + kInvSWords : kFwdWords + (kDyn ? 1 : 0);
+    __shared__ alignas(16) uint32_t lds[kLdsWords];   // (written as uint4 by the staging)
     uint32_t *const count = lds + kFwdWords;
     // Odd waves issue at a higher priority than even ones (a workgroup's
     // waves go to the CU's four SIMDs in turn, so two SIMDs run high and two
