@@ -134,6 +134,7 @@ int run(aesgpu_ctx *ctx, const LaunchArgs &a, aesgpu_stream_t stream) {
     LaunchArgs b = a;
     b.bpl = ctx->blocks_per_lane;
     b.max_tiles = ctx->max_tiles;
+    b.host_memory = ctx->host_memory;
     return launch(ctx->d_tables, ctx->n_cu, b, reinterpret_cast<hipStream_t>(stream));
 }
 

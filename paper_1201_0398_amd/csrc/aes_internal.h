@@ -66,12 +66,31 @@ struct LaunchArgs {
     int bpl;              // blocks per lane: 1, 2 or 4, or 0 to choose by size
     uint32_t max_tiles;   // most tiles per CU in one kernel launch (a longer call is
                           // split), 0 = kMaxTilesPerCu
+    bool host_memory;     // the blocks are read from or written to host memory
 };
 
 // A single-buffer kernel's workgroup hands out at most 16 * kMaxTilesPerCu
 // shares of work from a 16-bit LDS count; longer calls are split into several
 // launches.
 constexpr uint32_t kMaxTilesPerCu = 4096;
+
+// Whether a launch of `bpl` blocks per lane on n_bytes streams its blocks past
+// the caches: from the size on where input and output together are as large as
+// the 256 MB Infinity Cache, on device memory, and not at one block per lane
+// (whose launches are smaller, or were given that shape).  Measured (µs, cached /
+// streamed, three pairs of buffers in turn): AES-128 ECB encryption 128 MiB
+// 92.2 / 88.8, 190 MiB 132.8 / 129.5, 256 MiB 176.0 / 172.7, 1 GiB 680.8 / 675.6;
+// CTR 1 GiB 586 / 575; with a copy of the output behind it 128 MiB 145 / 129,
+// 190 MiB 199 / 195, 1 GiB 1022 / 1021.  A streamed call below that size is
+// faster too (64 MiB 45.6 / 42.3 with streamed stores), but whoever reads its
+// output next pays more than that (61.6 / 65.4; with 4 blocks per lane forced,
+// encryption and a copy: 16 MiB 24.3 / 26.1, 64 MiB 66.3 / 69.9, 96 MiB
+// 94.7 / 99.7).  A device of fewer CUs takes 2 or 4 blocks per lane from smaller
+// sizes on, and so does a context that is told to.
+constexpr uint64_t kStreamBytes = uint64_t(128) << 20;
+constexpr bool streams(int bpl, uint64_t n_bytes, bool host_memory) {
+    return bpl > 1 && n_bytes >= kStreamBytes && !host_memory;
+}
 
 // Enqueues the kernel for `a` on `stream`; returns an AESGPU status.
 int launch(const uint32_t *d_tables, int n_cu, const LaunchArgs &a, hipStream_t stream);
@@ -112,4 +131,5 @@ struct aesgpu_ctx {
                            // create), 0 = chosen by size
     uint32_t max_tiles;    // single-buffer launches: tiles per CU per launch
                            // (AESGPU_MAX_TILES_PER_CU at create), 0 = kMaxTilesPerCu
+    bool host_memory = false;   // calls on host memory (the pipeline's copy of a context)
 };

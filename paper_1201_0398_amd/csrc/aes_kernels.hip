@@ -113,27 +113,16 @@ __device__ __forceinline__ uint32_t lane_offset(const TileView &v, int j) {
     return (tile_slot<kWaveMajor, BPL>(v.w, j) - v.shift) * 16u;
 }
 
-// Kernels of 2 and 4 blocks per lane run on 128 MiB and more, input and output
-// as large as the 256 MB Infinity Cache together: they stream past the caches.
-// Measured (µs, cached / streamed, three pairs of buffers in turn): AES-128 ECB
-// encryption 128 MiB 92.2 / 88.8, 190 MiB 132.8 / 129.5, 256 MiB 176.0 / 172.7,
-// 1 GiB 680.8 / 675.6; CTR 1 GiB 586 / 575; with a copy of the output behind it
-// 128 MiB 145 / 129, 190 MiB 199 / 195, 1 GiB 1022 / 1021.  Streaming smaller
-// calls makes them faster too (64 MiB 45.6 / 42.3 with streamed stores), but
-// whoever reads their output next pays more than that (61.6 / 65.4).
-template <int BPL>
-constexpr int kBlockPolicy = BPL > 1 ? kStreamed : kCached;
-
-template <bool kWaveMajor, int BPL>
+template <bool kWaveMajor, int BPL, int kPolicy>
 __device__ __forceinline__ void load_tile(uint4 (&v)[BPL], const TileView &t) {
 #pragma unroll
     for (int j = 0; j < BPL; ++j)
-        v[j] = buffer_load16<kBlockPolicy<BPL>>(t.in, lane_offset<kWaveMajor, BPL>(t, j));
+        v[j] = buffer_load16<kPolicy>(t.in, lane_offset<kWaveMajor, BPL>(t, j));
 }
 
-template <bool kWaveMajor, int BPL>
+template <bool kWaveMajor, int BPL, int kPolicy>
 __device__ __forceinline__ void store_block(const TileView &t, int j, const uint4 &o) {
-    buffer_store16<kBlockPolicy<BPL>>(t.out, lane_offset<kWaveMajor, BPL>(t, j), o);
+    buffer_store16<kPolicy>(t.out, lane_offset<kWaveMajor, BPL>(t, j), o);
 }
 
 // Lane L gets x of lane L - 1 (a DPP shift of the wave); lane 0 keeps lane0.
@@ -276,8 +265,16 @@ __device__ __forceinline__ void rounds_v(const uint32_t *lds, const Bases &b, ui
 // kDyn: the waves claim the shares of the workgroup's tiles from a count in
 // LDS (launches with several tiles per CU); otherwise the workgroup has one tile
 // and wave i computes its share i.
-template <Op OP, int NR, int BPL, bool kDyn>
+// kShape: the blocks per lane, plus kBlocksCached where the blocks of 2 and 4 per
+// lane go through the caches instead of past them (see streams()).  (One template
+// for both: as a function shared by two kernels the same code kept fewer table
+// reads in flight and spilled more.)
+constexpr int kBlocksCached = 16;
+
+template <Op OP, int NR, int kShape, bool kDyn>
 __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
+    constexpr int BPL = kShape & (kBlocksCached - 1);
+    constexpr int kPolicy = kShape == 1 || kShape > kBlocksCached ? kCached : kStreamed;
     constexpr bool kInv = (OP == Op::kEcbDec || OP == Op::kCbcDec);
     constexpr bool kCtr = (OP == Op::kCtrBe32 || OP == Op::kCtrLe128);
     // CTR at 4 blocks per lane: a share's 256 counters start at a multiple of
@@ -331,7 +328,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
     uint4 next[BPL];
     uint4 next_prev = make_uint4(0, 0, 0, 0);   // CBC only
     TileView view = tile_view(p.in, p.out, tile_of(cur), cur & 15u, p.n_full, p.voff, tile);
-    if constexpr (!kKept) load_tile<kWM, BPL>(next, view);
+    if constexpr (!kKept) load_tile<kWM, BPL, kPolicy>(next, view);
     if constexpr (OP == Op::kCbcDec) {
         // (Launches with one share per wave never chain from block -1, and
         // with prev_in known to be 0 the compiler kept twice as many table
@@ -440,7 +437,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         uint4 in[BPL];
         if constexpr (kKept) {
             view = tile_view(p.in, p.out, base, w, p.n_full, p.voff, tile);
-            load_tile<kWM, BPL>(in, view);
+            load_tile<kWM, BPL, kPolicy>(in, view);
         } else {
 #pragma unroll
             for (int j = 0; j < BPL; ++j) in[j] = next[j];
@@ -449,7 +446,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
         const TileView now = view;
         if constexpr (!kKept) {
             view = tile_view(p.in, p.out, next_base, next_w, p.n_full, p.voff, tile);
-            load_tile<kWM, BPL>(next, view);
+            load_tile<kWM, BPL, kPolicy>(next, view);
         }
         if constexpr (OP == Op::kCbcDec)
             next_prev = load_wave_prev<BPL>(p.in, next_base, next_w, p.n_full, uint32_t(tile),
@@ -528,7 +525,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
                 o.z ^= q.z;
                 o.w ^= q.w;
             }
-            store_block<kWM, BPL>(now, j, o);
+            store_block<kWM, BPL, kPolicy>(now, j, o);
         }
     };
     // The shares of a partial last tile with no block are not computed: a
@@ -569,7 +566,7 @@ __global__ __launch_bounds__(kWG) void aes_kernel(Params p) {
 }
 
 template <Op OP, int NR, int BPL>
-int launch_part(Params p, int n_cu, hipStream_t stream) {
+int launch_part(Params p, int n_cu, bool streamed, hipStream_t stream) {
     // CTR: shift the mapping so every wave's 64 * BPL counters start at a
     // multiple of 64 * BPL (so they differ only in their low byte).
     if constexpr (OP == Op::kCtrBe32) {
@@ -605,9 +602,13 @@ int launch_part(Params p, int n_cu, hipStream_t stream) {
     // the same time): such launches at one block per lane keep one share per
     // wave, unless they are a later part of a split CBC call.
     const void *kernel = reinterpret_cast<const void *>(&aes_kernel<OP, NR, BPL, true>);
-    if constexpr (BPL == 1)
+    if constexpr (BPL == 1) {
         if (tiles <= uint64_t(n_cu) && !p.prev_in)
             kernel = reinterpret_cast<const void *>(&aes_kernel<OP, NR, BPL, false>);
+    } else {
+        if (!streamed)
+            kernel = reinterpret_cast<const void *>(&aes_kernel<OP, NR, BPL + kBlocksCached, true>);
+    }
     // The launch's own status (the thread's last-error state may hold an
     // earlier, unrelated failure).
     void *args[] = {&p};
@@ -622,7 +623,7 @@ int launch_part(Params p, int n_cu, hipStream_t stream) {
 // shift is the same in every part; a later CBC part chains from the block
 // before it, and only the last part has the CTR tail.
 template <Op OP, int NR, int BPL>
-int launch_one(const Params &p, int n_cu, uint32_t max_tiles, hipStream_t stream) {
+int launch_one(const Params &p, int n_cu, uint32_t max_tiles, bool streamed, hipStream_t stream) {
     const uint64_t part = uint64_t(max_tiles - 1) * uint64_t(n_cu) * uint64_t(kWG) * BPL;
     Params q = p;
     for (uint64_t done = 0;; done += part) {
@@ -634,24 +635,25 @@ int launch_one(const Params &p, int n_cu, uint32_t max_tiles, hipStream_t stream
         q.ctr0 = p.ctr0 + uint32_t(done);
         q.index0 = p.index0 + done;
         q.prev_in = done > 0 ? 1u : p.prev_in;
-        const int st = launch_part<OP, NR, BPL>(q, n_cu, stream);
+        const int st = launch_part<OP, NR, BPL>(q, n_cu, streamed, stream);
         if (st != AESGPU_OK || last) return st;
     }
 }
 
 template <Op OP, int BPL>
-int launch_nr(const Params &p, uint32_t nr, int n_cu, uint32_t max_tiles, hipStream_t stream) {
+int launch_nr(const Params &p, uint32_t nr, int n_cu, uint32_t max_tiles, bool streamed,
+              hipStream_t stream) {
     switch (nr) {
-        case 10: return launch_one<OP, 10, BPL>(p, n_cu, max_tiles, stream);
-        case 12: return launch_one<OP, 12, BPL>(p, n_cu, max_tiles, stream);
-        case 14: return launch_one<OP, 14, BPL>(p, n_cu, max_tiles, stream);
+        case 10: return launch_one<OP, 10, BPL>(p, n_cu, max_tiles, streamed, stream);
+        case 12: return launch_one<OP, 12, BPL>(p, n_cu, max_tiles, streamed, stream);
+        case 14: return launch_one<OP, 14, BPL>(p, n_cu, max_tiles, streamed, stream);
         default: return AESGPU_EINVAL;
     }
 }
 
 template <Op OP>
 int launch_op(const Params &p, uint32_t nr, int n_cu, int forced_bpl, uint32_t max_tiles,
-              hipStream_t stream) {
+              bool host_memory, hipStream_t stream) {
     int bpl = forced_bpl;
     if (bpl != 1 && bpl != 2 && bpl != 4) {
         // Every lane computes all its slots, empty or not, and a workgroup
@@ -677,10 +679,11 @@ int launch_op(const Params &p, uint32_t nr, int n_cu, int forced_bpl, uint32_t m
         // at 1 GiB.
         if (OP == Op::kCbcDec && nr >= 12 && bpl == 4) bpl = 2;
     }
+    const bool streamed = streams(bpl, 16 * p.n_full, host_memory);
     switch (bpl) {
-        case 1: return launch_nr<OP, 1>(p, nr, n_cu, max_tiles, stream);
-        case 2: return launch_nr<OP, 2>(p, nr, n_cu, max_tiles, stream);
-        default: return launch_nr<OP, 4>(p, nr, n_cu, max_tiles, stream);
+        case 1: return launch_nr<OP, 1>(p, nr, n_cu, max_tiles, streamed, stream);
+        case 2: return launch_nr<OP, 2>(p, nr, n_cu, max_tiles, streamed, stream);
+        default: return launch_nr<OP, 4>(p, nr, n_cu, max_tiles, streamed, stream);
     }
 }
 
@@ -701,11 +704,11 @@ int launch(const uint32_t *d_tables, int n_cu, const LaunchArgs &a, hipStream_t 
     const uint32_t mt = a.max_tiles >= 2 && a.max_tiles <= kMaxTilesPerCu ? a.max_tiles
                                                                           : kMaxTilesPerCu;
     switch (a.op) {
-        case Op::kEcbEnc: return launch_op<Op::kEcbEnc>(p, a.nr, n_cu, a.bpl, mt, stream);
-        case Op::kEcbDec: return launch_op<Op::kEcbDec>(p, a.nr, n_cu, a.bpl, mt, stream);
-        case Op::kCtrBe32: return launch_op<Op::kCtrBe32>(p, a.nr, n_cu, a.bpl, mt, stream);
-        case Op::kCtrLe128: return launch_op<Op::kCtrLe128>(p, a.nr, n_cu, a.bpl, mt, stream);
-        case Op::kCbcDec: return launch_op<Op::kCbcDec>(p, a.nr, n_cu, a.bpl, mt, stream);
+        case Op::kEcbEnc: return launch_op<Op::kEcbEnc>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
+        case Op::kEcbDec: return launch_op<Op::kEcbDec>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
+        case Op::kCtrBe32: return launch_op<Op::kCtrBe32>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
+        case Op::kCtrLe128: return launch_op<Op::kCtrLe128>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
+        case Op::kCbcDec: return launch_op<Op::kCbcDec>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
     }
     return AESGPU_EINVAL;
 }

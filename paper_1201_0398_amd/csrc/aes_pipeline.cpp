@@ -324,11 +324,12 @@ int aesgpu_pipeline_run(aesgpu_pipeline *pl, const aesgpu_key *key, const aesgpu
     const uintptr_t dev_in = pinned_device_address(h_in, n_bytes);
     const uintptr_t dev_out = pinned_device_address(h_out, n_bytes);
     const bool pinned_in = dev_in != 0, pinned_out = dev_out != 0;
-    // Kernels on host memory run at one block per lane whatever the size: those of
-    // more stream past the caches, which suits device memory only (1 GiB of
-    // pinned memory: ECB 24.05 ms at 4 blocks per lane, 24.3 streamed, 23.6 at
-    // one; CTR 23.4, 23.9 and 22.9).
+    // Kernels on host memory run at one block per lane whatever the size, unless
+    // the context was told otherwise, and never stream past the caches, which
+    // suits device memory only (1 GiB of pinned memory: ECB 24.05 ms at 4 blocks
+    // per lane, 24.3 streamed, 23.6 at one; CTR 23.4, 23.9 and 22.9).
     aesgpu_ctx one = *pl->ctx;
+    one.host_memory = true;
     if (one.blocks_per_lane == 0) one.blocks_per_lane = 1;
     if (pinned_in && pinned_out && !(pl->flags & AESGPU_PIPELINE_COPY) && dev_in % 16 == 0 &&
         dev_out % 16 == 0) {
