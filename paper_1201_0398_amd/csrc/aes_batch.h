@@ -92,6 +92,10 @@ inline void set_totals(BatchLaunch &L, const BatchTotals &t) {
     }
 }
 
+// Blocks per tile where the caller leaves it to the library, for messages not yet
+// validated.
+uint32_t default_tile_blocks(int n_cu, const aesgpu_msg *msgs, size_t m);
+
 // Validates messages and cuts them into tiles of at most tile_blocks blocks,
 // each queue sorted longest first; CBC-encrypt messages form groups (per key
 // size, longest first, listed in cbc_list) for their own launch.

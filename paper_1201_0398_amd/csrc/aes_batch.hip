@@ -1423,6 +1423,34 @@ void sort_longest_first(std::vector<Tile> &t, uint32_t tile_blocks) {
 
 }  // namespace
 
+// Blocks per tile where the caller leaves it to the library: about two tiles
+// for every wave of the chip, 256 to kDefaultTileBlocks blocks.  A wave needs
+// tens of microseconds for some thousand blocks, so with one size for all the
+// time of a small batch was that of its longest tile; tiles below 256 blocks
+// give up the whole steps and pay a key expansion for little work.  Measured
+// with lists and no graph, us at 256 / 512 / 1024 / 2048 / 8192 blocks per tile:
+// 256 messages, 23 MB 33 / 34 / 41 / 64 / 211; 1,146 messages, 83 MB
+// 82 / 79 / 78 / 92 / 220; 4,096 messages, 111 MB 106 / 98 / 96 / 102 / 218;
+// 7,459 messages, 640 MB decrypted 702 / 606 / 570 / 575 / 593.  At the other end
+// 4096 blocks leave a large batch's end less uneven than 8192 (65,536 messages up
+// to 1 MiB: 4413 against 4489 us, 4535 against 4597 on another machine).
+namespace {
+constexpr uint64_t kTilesPerWave = 2;
+constexpr uint32_t kDefaultTileBlocks = 4096;
+}  // namespace
+
+uint32_t default_tile_blocks(int n_cu, const aesgpu_msg *msgs, size_t m) {
+    // (CBC-encrypt messages are not cut into tiles: their groups have a launch of
+    // their own.)
+    uint64_t blocks = 0;
+    for (size_t i = 0; i < m && blocks < (uint64_t(1) << 40); ++i)
+        if (msgs[i].mode != AESGPU_MODE_CBC || msgs[i].dir != AESGPU_DIR_ENCRYPT)
+            blocks += (std::min<uint64_t>(msgs[i].n_bytes, uint64_t(1) << 50) + 15) / 16;
+    const uint64_t waves = uint64_t(n_cu) * (kWG / 64);
+    const uint64_t t = (blocks / (waves * kTilesPerWave) + 255) / 256 * 256;
+    return uint32_t(std::min<uint64_t>(std::max<uint64_t>(t, 256), kDefaultTileBlocks));
+}
+
 int build_tiles(const aesgpu_msg *msgs, size_t m, uint32_t tile_blocks, std::vector<DevMsg> &dm,
                 std::vector<Tile> (&tiles)[2], std::vector<uint32_t> &cbc_list,
                 std::vector<Tile> &cbc_groups, BatchTotals &tot) {
@@ -1523,29 +1551,7 @@ using namespace aesgpu;
 
 namespace {
 constexpr uint32_t kDefaultBpl = 4;
-constexpr uint32_t kDefaultTileBlocks = 4096;
 constexpr uint32_t kFewTileBlocks = 8192;   // for batches whose descriptors fill the scratch
-
-// Blocks per tile where the caller leaves it to the library: about two tiles
-// for every wave of the chip, 256 to kDefaultTileBlocks blocks.  A wave needs
-// tens of microseconds for some thousand blocks, so with one size for all the
-// time of a small batch was that of its longest tile; tiles below 256 blocks
-// give up the whole steps and pay a key expansion for little work.  Measured
-// with lists and no graph, us at 256 / 512 / 1024 / 2048 / 8192 blocks per tile:
-// 256 messages, 23 MB 33 / 34 / 41 / 64 / 211; 1,146 messages, 83 MB
-// 82 / 79 / 78 / 92 / 220; 4,096 messages, 111 MB 106 / 98 / 96 / 102 / 218;
-// 7,459 messages, 640 MB decrypted 702 / 606 / 570 / 575 / 593.  At the other end
-// 4096 blocks leave a large batch's end less uneven than 8192 (65,536 messages up
-// to 1 MiB: 4413 against 4489 us, 4535 against 4597 on another machine).
-constexpr uint64_t kTilesPerWave = 2;
-uint32_t default_tile_blocks(const aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m) {
-    uint64_t blocks = 0;
-    for (size_t i = 0; i < m && blocks < (uint64_t(1) << 40); ++i)
-        blocks += std::min<uint64_t>(msgs[i].n_bytes, uint64_t(1) << 50) / 16;
-    const uint64_t waves = uint64_t(ctx->n_cu) * (kWG / 64);
-    const uint64_t t = (blocks / (waves * kTilesPerWave) + 255) / 256 * 256;
-    return uint32_t(std::min<uint64_t>(std::max<uint64_t>(t, 256), kDefaultTileBlocks));
-}
 }  // namespace
 
 // Descriptor scratch of aesgpu_batch_run_noalloc(): one copy on each GPU the
@@ -1580,7 +1586,7 @@ size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 struct aesgpu_batch {
     aesgpu_ctx *ctx = nullptr;
     uint32_t bpl = kDefaultBpl;
-    uint32_t tile_blocks = kDefaultTileBlocks;
+    uint32_t tile_blocks = 0;
     size_t n_msgs = 0;
     size_t n_tiles[2] = {0, 0};    // forward, inverse
     BatchTotals tot;
@@ -1662,7 +1668,7 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     uint32_t bpl, tile_blocks;
     const int shape = batch_shape(cfg, bpl, tile_blocks);
     if (shape != AESGPU_OK) return shape;
-    if (!tile_blocks) tile_blocks = default_tile_blocks(ctx, msgs, m);
+    if (!tile_blocks) tile_blocks = default_tile_blocks(ctx->n_cu, msgs, m);
 
     std::vector<DevMsg> dm;
     std::vector<Tile> tiles[2];
@@ -1802,7 +1808,7 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     thread_local std::vector<uint8_t> staging;
     BatchTotals tot;
     const bool choose = tile_blocks == 0;
-    if (choose) tile_blocks = default_tile_blocks(ctx, msgs, m);
+    if (choose) tile_blocks = default_tile_blocks(ctx->n_cu, msgs, m);
     int st = build_tiles(msgs, m, tile_blocks, dm, tiles, cbc_list, cbc_groups, tot);
     if (st != AESGPU_OK) return st;
     if (tiles[0].size() + tiles[1].size() + cbc_groups.size() == 0) return AESGPU_OK;
