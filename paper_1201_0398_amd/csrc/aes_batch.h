@@ -42,14 +42,14 @@ constexpr uint32_t kCbcGroupMsgs = 16;
 // followed by 64 equivalent-inverse-cipher words.
 constexpr uint32_t kSchedWords = 128;
 
-// Device bytes of a launch's counters, in words: queue q's count of pulled
-// tiles at word 32 * q and the count of workgroups that have finished at
-// kExitWord, each on a 128-byte line of its own.  The counters must be zero
-// before the first launch; the last workgroup of every launch zeroes them
-// again.
-constexpr size_t kCounterBytes = 4 * (2 + 1024) + 56;
+// A launch's counters in device memory: queue q's count of pulled tiles at word
+// kQueueStride * q and the count of workgroups that have finished at kExitWord,
+// each on a 128-byte line of its own that holds nothing else (the counters lie
+// at a multiple of 128 bytes).  They must be zero before the first launch; the
+// last workgroup of every launch zeroes them again.
 constexpr uint32_t kQueueStride = 32;
-constexpr uint32_t kExitWord = 2 + 1024;
+constexpr uint32_t kExitWord = 2 * kQueueStride;
+constexpr size_t kCounterBytes = 3 * kQueueStride * 4;
 
 struct BatchTotals {
     uint64_t total = 0;    // sum of message bytes
@@ -102,6 +102,26 @@ uint32_t default_tile_blocks(int n_cu, const aesgpu_msg *msgs, size_t m);
 int build_tiles(const aesgpu_msg *msgs, size_t m, uint32_t tile_blocks, std::vector<DevMsg> &dm,
                 std::vector<Tile> (&tiles)[2], std::vector<uint32_t> &cbc_list,
                 std::vector<Tile> &cbc_groups, BatchTotals &tot);
+
+// Where a batch's descriptors lie in one piece of device memory, in bytes from
+// its start (which is 256-byte aligned): the counters first, every part at a
+// multiple of 256.
+constexpr size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
+
+struct BatchLayout {
+    static constexpr size_t counters = 0;
+    static constexpr size_t msgs = align256(kCounterBytes);
+    size_t tiles[2], cbc_groups, cbc_dummy, cbc_list, total;
+
+    BatchLayout(size_t n_msgs, size_t n_forward, size_t n_inverse, size_t n_groups, size_t n_list) {
+        tiles[0] = msgs + align256(n_msgs * sizeof(DevMsg));
+        tiles[1] = tiles[0] + align256(n_forward * sizeof(Tile));
+        cbc_groups = tiles[1] + align256(n_inverse * sizeof(Tile));
+        cbc_dummy = cbc_groups + align256(n_groups * sizeof(Tile));   // 16 bytes, see BatchLaunch
+        cbc_list = cbc_dummy + align256(16);
+        total = cbc_list + n_list * sizeof(uint32_t);
+    }
+};
 
 // One persistent launch over both queues, then (if the batch has CBC-encrypt
 // messages) the CBC-encryption launch.

@@ -1579,8 +1579,6 @@ void *scratch_address(int device) {
     return g_scratch_ptr[device];
 }
 
-size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
-
 }  // namespace
 
 struct aesgpu_batch {
@@ -1590,7 +1588,7 @@ struct aesgpu_batch {
     size_t n_msgs = 0;
     size_t n_tiles[2] = {0, 0};    // forward, inverse
     BatchTotals tot;
-    void *d_mem = nullptr;         // messages | forward tiles | inverse tiles | counters
+    void *d_mem = nullptr;         // the descriptors, laid out as in BatchLayout
     DevMsg *d_msgs = nullptr;
     Tile *d_tiles[2] = {nullptr, nullptr};
     uint32_t *d_counters = nullptr;
@@ -1697,25 +1695,19 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
         delete b;
         return AESGPU_EHIP;
     }
-    const size_t msg_bytes = m * sizeof(DevMsg);
-    const size_t t0 = tiles[0].size() * sizeof(Tile), t1 = tiles[1].size() * sizeof(Tile);
-    const size_t cg = cbc_groups.size() * sizeof(Tile);
-    const size_t cl = cbc_list.size() * sizeof(uint32_t);
-    const size_t dummy = cg ? 16 : 0;
-    const size_t bytes = msg_bytes + t0 + t1 + kCounterBytes + cg + dummy + cl;
+    const BatchLayout at(m, tiles[0].size(), tiles[1].size(), cbc_groups.size(), cbc_list.size());
+    const size_t bytes = at.total;
     if (hipMalloc(&b->d_mem, bytes) != hipSuccess) {
         delete b;
         return AESGPU_ENOMEM;
     }
     char *base = static_cast<char *>(b->d_mem);
-    b->d_msgs = reinterpret_cast<DevMsg *>(base);
-    b->d_tiles[0] = reinterpret_cast<Tile *>(base + msg_bytes);
-    b->d_tiles[1] = reinterpret_cast<Tile *>(base + msg_bytes + t0);
-    b->d_counters = reinterpret_cast<uint32_t *>(base + msg_bytes + t0 + t1);
-    b->d_cbc_groups = reinterpret_cast<Tile *>(base + msg_bytes + t0 + t1 + kCounterBytes);
-    b->d_cbc_dummy = reinterpret_cast<uint4 *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg);
-    b->d_cbc_list =
-        reinterpret_cast<uint32_t *>(base + msg_bytes + t0 + t1 + kCounterBytes + cg + dummy);
+    b->d_counters = reinterpret_cast<uint32_t *>(base + at.counters);
+    b->d_msgs = reinterpret_cast<DevMsg *>(base + at.msgs);
+    for (int q = 0; q < 2; ++q) b->d_tiles[q] = reinterpret_cast<Tile *>(base + at.tiles[q]);
+    b->d_cbc_groups = reinterpret_cast<Tile *>(base + at.cbc_groups);
+    b->d_cbc_dummy = reinterpret_cast<uint4 *>(base + at.cbc_dummy);
+    b->d_cbc_list = reinterpret_cast<uint32_t *>(base + at.cbc_list);
     // The queue counters start at zero once; every launch leaves them zero.
     // A copy from pageable memory takes about 10 us whatever its size: a small
     // plan is put together on the host and goes up in one (256 messages: 80 us,
@@ -1728,12 +1720,13 @@ int aesgpu_batch_plan(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     };
     constexpr size_t kOneUploadBytes = size_t(256) << 10;
     static const char zero[kCounterBytes] = {};
-    const Part parts[] = {{b->d_msgs, dm.data(), msg_bytes},
-                          {b->d_tiles[0], tiles[0].data(), t0},
-                          {b->d_tiles[1], tiles[1].data(), t1},
-                          {b->d_counters, zero, kCounterBytes},
-                          {b->d_cbc_groups, cbc_groups.data(), cg},
-                          {b->d_cbc_list, cbc_list.data(), cl}};
+    const Part parts[] = {
+        {b->d_counters, zero, kCounterBytes},
+        {b->d_msgs, dm.data(), m * sizeof(DevMsg)},
+        {b->d_tiles[0], tiles[0].data(), tiles[0].size() * sizeof(Tile)},
+        {b->d_tiles[1], tiles[1].data(), tiles[1].size() * sizeof(Tile)},
+        {b->d_cbc_groups, cbc_groups.data(), cbc_groups.size() * sizeof(Tile)},
+        {b->d_cbc_list, cbc_list.data(), cbc_list.size() * sizeof(uint32_t)}};
     bool ok = true;
     if (bytes <= kOneUploadBytes) {
         const std::unique_ptr<char[]> image(new (std::nothrow) char[bytes]());
@@ -1814,37 +1807,29 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     if (tiles[0].size() + tiles[1].size() + cbc_groups.size() == 0) return AESGPU_OK;
     const int chk = check_run(tot, d_keys, n_key_slots, d_in, in_bytes, d_out, out_bytes);
     if (chk != AESGPU_OK) return chk;
-    // Scratch layout, each part 256-byte aligned: queue counters (zero, as the
-    // batch kernel expects before a launch), messages, forward tiles, inverse
-    // tiles, CBC-encryption groups, 16 dummy bytes, CBC list.
-    size_t o_msgs, o_t0, o_t1, o_cg, o_dummy, o_cl, total;
-    for (;;) {
-        o_msgs = align256(kCounterBytes);
-        o_t0 = o_msgs + align256(m * sizeof(DevMsg));
-        o_t1 = o_t0 + align256(tiles[0].size() * sizeof(Tile));
-        o_cg = o_t1 + align256(tiles[1].size() * sizeof(Tile));
-        o_dummy = o_cg + align256(cbc_groups.size() * sizeof(Tile));
-        o_cl = o_dummy + 256;
-        total = o_cl + cbc_list.size() * sizeof(uint32_t);
-        if (total <= AESGPU_NOALLOC_SCRATCH_BYTES) break;
+    auto layout = [&] {
+        return BatchLayout(m, tiles[0].size(), tiles[1].size(), cbc_groups.size(), cbc_list.size());
+    };
+    BatchLayout at = layout();
+    if (at.total > AESGPU_NOALLOC_SCRATCH_BYTES && choose) {
         // The library's own choice of tiles must not cost a batch its place.
-        if (!choose || tile_blocks == kFewTileBlocks) return AESGPU_ESCRATCH;
-        tile_blocks = kFewTileBlocks;
-        st = build_tiles(msgs, m, tile_blocks, dm, tiles, cbc_list, cbc_groups, tot);
+        st = build_tiles(msgs, m, kFewTileBlocks, dm, tiles, cbc_list, cbc_groups, tot);
         if (st != AESGPU_OK) return st;
+        at = layout();
     }
-    // The queue counters must start at zero; the padding between parts is
-    // never read.
-    staging.resize(total);
+    if (at.total > AESGPU_NOALLOC_SCRATCH_BYTES) return AESGPU_ESCRATCH;
+    // The counters must start at zero; the padding between parts is never read.
+    staging.resize(at.total);
     uint8_t *h = staging.data();
-    std::memset(h, 0, kCounterBytes);
-    if (m) std::memcpy(h + o_msgs, dm.data(), m * sizeof(DevMsg));
-    if (!tiles[0].empty()) std::memcpy(h + o_t0, tiles[0].data(), tiles[0].size() * sizeof(Tile));
-    if (!tiles[1].empty()) std::memcpy(h + o_t1, tiles[1].data(), tiles[1].size() * sizeof(Tile));
+    std::memset(h + at.counters, 0, kCounterBytes);
+    if (m) std::memcpy(h + at.msgs, dm.data(), m * sizeof(DevMsg));
+    for (int q = 0; q < 2; ++q)
+        if (!tiles[q].empty())
+            std::memcpy(h + at.tiles[q], tiles[q].data(), tiles[q].size() * sizeof(Tile));
     if (!cbc_groups.empty())
-        std::memcpy(h + o_cg, cbc_groups.data(), cbc_groups.size() * sizeof(Tile));
+        std::memcpy(h + at.cbc_groups, cbc_groups.data(), cbc_groups.size() * sizeof(Tile));
     if (!cbc_list.empty())
-        std::memcpy(h + o_cl, cbc_list.data(), cbc_list.size() * sizeof(uint32_t));
+        std::memcpy(h + at.cbc_list, cbc_list.data(), cbc_list.size() * sizeof(uint32_t));
 
     DeviceGuard g(ctx->device);
     if (!g.ok()) return AESGPU_EHIP;
@@ -1853,22 +1838,22 @@ int aesgpu_batch_run_noalloc(aesgpu_ctx *ctx, const aesgpu_msg *msgs, size_t m,
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // From pageable host memory, so the copy has read `staging` when the
     // call returns; it runs in stream order before the launches.
-    if (hipMemcpyAsync(d, h, total, hipMemcpyHostToDevice, s) != hipSuccess) return AESGPU_EHIP;
+    if (hipMemcpyAsync(d, h, at.total, hipMemcpyHostToDevice, s) != hipSuccess) return AESGPU_EHIP;
     BatchLaunch L{};
-    L.msgs = reinterpret_cast<const DevMsg *>(d + o_msgs);
-    L.tiles[0] = reinterpret_cast<const Tile *>(d + o_t0);
-    L.tiles[1] = reinterpret_cast<const Tile *>(d + o_t1);
-    L.n_tiles[0] = uint32_t(tiles[0].size());
-    L.n_tiles[1] = uint32_t(tiles[1].size());
-    L.counters = reinterpret_cast<uint32_t *>(d);
+    L.msgs = reinterpret_cast<const DevMsg *>(d + at.msgs);
+    for (int q = 0; q < 2; ++q) {
+        L.tiles[q] = reinterpret_cast<const Tile *>(d + at.tiles[q]);
+        L.n_tiles[q] = uint32_t(tiles[q].size());
+    }
+    L.counters = reinterpret_cast<uint32_t *>(d + at.counters);
     L.keys = d_keys;
     L.sched = nullptr;
     L.in = static_cast<const uint8_t *>(d_in);
     L.out = static_cast<uint8_t *>(d_out);
     L.tables = ctx->d_tables;
-    L.cbc_list = reinterpret_cast<const uint32_t *>(d + o_cl);
-    L.cbc_groups = reinterpret_cast<const Tile *>(d + o_cg);
-    L.cbc_dummy = reinterpret_cast<uint4 *>(d + o_dummy);
+    L.cbc_list = reinterpret_cast<const uint32_t *>(d + at.cbc_list);
+    L.cbc_groups = reinterpret_cast<const Tile *>(d + at.cbc_groups);
+    L.cbc_dummy = reinterpret_cast<uint4 *>(d + at.cbc_dummy);
     L.n_cbc_groups = uint32_t(cbc_groups.size());
     L.n_cu = ctx->n_cu;
     L.bpl = bpl;
