@@ -149,7 +149,7 @@ int aesgpu_cbc_decrypt(aesgpu_ctx *ctx, const aesgpu_key *key, const uint8_t *iv
                        const void *d_in, void *d_out, size_t n_blocks, aesgpu_stream_t stream);
 
 /* ------------------------------------------------------------------------ */
-/* Batched messages: one persistent launch per table set                     */
+/* Batched messages: one persistent launch for both table sets               */
 /* ------------------------------------------------------------------------ */
 
 enum { AESGPU_MODE_ECB = 0, AESGPU_MODE_CTR = 1, AESGPU_MODE_CBC = 2 };
@@ -175,7 +175,7 @@ typedef struct {
     uint64_t n_bytes;
     uint32_t key_slot;
     uint16_t key_bits;   /* 128, 192 or 256 */
-    uint8_t mode;        /* AESGPU_MODE_ECB or AESGPU_MODE_CTR */
+    uint8_t mode;        /* AESGPU_MODE_ECB, AESGPU_MODE_CTR or AESGPU_MODE_CBC */
     uint8_t dir;         /* AESGPU_DIR_ENCRYPT or AESGPU_DIR_DECRYPT */
     uint8_t nonce[12];
     uint32_t ctr0;
@@ -184,8 +184,9 @@ typedef struct {
 #define AESGPU_BATCH_NO_GRAPH 1u /* launches without a hipGraph, which all are: no effect */
 
 /* Launch shape of a batch; zero fields take the defaults (4 blocks per lane,
- * and tiles of 256 to 4096 blocks, by the size of the batch).  tile_blocks must
- * be a multiple of 64 * blocks_per_lane. */
+ * and tiles of 256 to 4096 blocks, by the size of the batch: two for every wave of
+ * the GPU, CBC encryption aside, which has no tiles).  tile_blocks must be a multiple
+ * of 64 * blocks_per_lane. */
 typedef struct {
     uint32_t blocks_per_lane; /* 1, 2 or 4 (decryption tiles run at 2 where it is 4) */
     uint32_t tile_blocks;
@@ -195,7 +196,7 @@ typedef struct {
 typedef struct {
     uint64_t n_msgs;
     uint64_t n_tiles_forward;  /* ECB-encrypt and CTR tiles */
-    uint64_t n_tiles_inverse;  /* ECB-decrypt tiles */
+    uint64_t n_tiles_inverse;  /* ECB-decrypt and CBC-decrypt tiles */
     uint64_t total_bytes;      /* sum of n_bytes */
     uint64_t in_bytes_needed;  /* max(in_off + n_bytes) */
     uint64_t out_bytes_needed; /* max(out_off + n_bytes) */
@@ -250,7 +251,8 @@ int aesgpu_batch_run(aesgpu_batch *plan, const uint8_t *d_keys, size_t n_key_slo
  * AESGPU_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until
  * the process ends; a batch needing more returns AESGPU_ESCRATCH before any
  * HIP call (65,536 messages of up to 1 MiB in 8192-block tiles need about
- * 6 MB).  The descriptors are built on the host and copied on `stream` from
+ * 6 MB; where the tiles are the library's choice and would not fit, it takes
+ * 8192-block ones).  The descriptors are built on the host and copied on `stream` from
  * pageable host memory (a copy that completes before the call returns).
  * Every call on one GPU uses that GPU's one scratch area: calls whose runs
  * overlap in time on one GPU (other streams, other contexts, other threads)

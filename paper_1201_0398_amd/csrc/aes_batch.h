@@ -63,7 +63,7 @@ struct BatchTotals {
 };
 
 // Everything one batched run needs on the device.  Set 0 is the forward
-// table set (ECB encryption, CTR), set 1 the inverse set (ECB decryption).
+// table set (ECB encryption, CTR), set 1 the inverse set (ECB and CBC decryption).
 // Both sets run in one launch.
 struct BatchLaunch {
     const DevMsg *msgs;

@@ -1,6 +1,7 @@
 // Batched AES: many messages of uneven length, each with its own key, key
-// size and mode, in one persistent launch per LDS table set, with the key
-// schedules expanded on the device inside the launch.
+// size and mode, in one persistent launch for both LDS table sets (and one of its
+// own for CBC encryption), with the key schedules expanded on the device inside
+// the launch.
 //
 // * Host plan: every message is cut into message-pure tiles of at most
 //   `tile_blocks` blocks.  Tiles that need the forward tables (ECB
@@ -1229,10 +1230,10 @@ __device__ void serve_ring(const uint32_t *lds, const Bases &b, const ResidentLa
             // stores are complete, with no L2 invalidation or write-back (a
             // fence at this scope costs one per tile, and those serialise).
             // Short tiles (small requests, whose latency they are) issue before long
-            // ones, and both before waves that poll.  p50 / p99 at 340 k req/s 70 / 642 us -> 64 / 637, at
-            // 170 k 56 / 334 -> 54 / 331; saturation the same.  With long tiles at
-            // the pollers' priority p50 fell to 62 and p99 rose to 649; with one
-            // priority for all tiles neither moved.
+            // ones, and both before waves that poll.  p50 / p99 at 340 k req/s
+            // 70 / 642 us -> 64 / 637, at 170 k 56 / 334 -> 54 / 331; saturation the
+            // same.  With long tiles at the pollers' priority p50 fell to 62 and p99
+            // rose to 649; with one priority for all tiles neither moved.
             if (r.n_blocks <= kShortTile)
                 __builtin_amdgcn_s_setprio(3);
             else

@@ -623,7 +623,8 @@ int launch_part(Params p, int n_cu, bool streamed, hipStream_t stream) {
 // shift is the same in every part; a later CBC part chains from the block
 // before it, and only the last part has the CTR tail.
 template <Op OP, int NR, int BPL>
-int launch_one(const Params &p, int n_cu, uint32_t max_tiles, bool streamed, hipStream_t stream) {
+int launch_one(const Params &p, int n_cu, uint32_t max_tiles, bool streamed,
+               hipStream_t stream) {
     const uint64_t part = uint64_t(max_tiles - 1) * uint64_t(n_cu) * uint64_t(kWG) * BPL;
     Params q = p;
     for (uint64_t done = 0;; done += part) {
@@ -652,9 +653,10 @@ int launch_nr(const Params &p, uint32_t nr, int n_cu, uint32_t max_tiles, bool s
 }
 
 template <Op OP>
-int launch_op(const Params &p, uint32_t nr, int n_cu, int forced_bpl, uint32_t max_tiles,
-              bool host_memory, hipStream_t stream) {
-    int bpl = forced_bpl;
+int launch_op(const Params &p, const LaunchArgs &a, int n_cu, uint32_t max_tiles,
+              hipStream_t stream) {
+    const uint32_t nr = a.nr;
+    int bpl = a.bpl;
     if (bpl != 1 && bpl != 2 && bpl != 4) {
         // Every lane computes all its slots, empty or not, and a workgroup
         // overlaps a tile's rounds with the next tile's loads only when it has
@@ -679,7 +681,7 @@ int launch_op(const Params &p, uint32_t nr, int n_cu, int forced_bpl, uint32_t m
         // at 1 GiB.
         if (OP == Op::kCbcDec && nr >= 12 && bpl == 4) bpl = 2;
     }
-    const bool streamed = streams(bpl, 16 * p.n_full, host_memory);
+    const bool streamed = streams(bpl, 16 * p.n_full, a.host_memory);
     switch (bpl) {
         case 1: return launch_nr<OP, 1>(p, nr, n_cu, max_tiles, streamed, stream);
         case 2: return launch_nr<OP, 2>(p, nr, n_cu, max_tiles, streamed, stream);
@@ -704,11 +706,11 @@ int launch(const uint32_t *d_tables, int n_cu, const LaunchArgs &a, hipStream_t 
     const uint32_t mt = a.max_tiles >= 2 && a.max_tiles <= kMaxTilesPerCu ? a.max_tiles
                                                                           : kMaxTilesPerCu;
     switch (a.op) {
-        case Op::kEcbEnc: return launch_op<Op::kEcbEnc>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
-        case Op::kEcbDec: return launch_op<Op::kEcbDec>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
-        case Op::kCtrBe32: return launch_op<Op::kCtrBe32>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
-        case Op::kCtrLe128: return launch_op<Op::kCtrLe128>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
-        case Op::kCbcDec: return launch_op<Op::kCbcDec>(p, a.nr, n_cu, a.bpl, mt, a.host_memory, stream);
+        case Op::kEcbEnc: return launch_op<Op::kEcbEnc>(p, a, n_cu, mt, stream);
+        case Op::kEcbDec: return launch_op<Op::kEcbDec>(p, a, n_cu, mt, stream);
+        case Op::kCtrBe32: return launch_op<Op::kCtrBe32>(p, a, n_cu, mt, stream);
+        case Op::kCtrLe128: return launch_op<Op::kCtrLe128>(p, a, n_cu, mt, stream);
+        case Op::kCbcDec: return launch_op<Op::kCbcDec>(p, a, n_cu, mt, stream);
     }
     return AESGPU_EINVAL;
 }

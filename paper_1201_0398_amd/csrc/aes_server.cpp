@@ -310,9 +310,11 @@ int launch_slot(aesgpu_server *s, Slot &slot, bool backlog) {
         // Adaptive: about two tiles per wave slot of this batch's share of
         // the CUs (the chip divided among it and the batches already in
         // flight), so that a small batch is still spread over many waves (a
-        // lone wave on a long tile is latency bound) while batches of the
-        // other streams keep CUs to run on; between one step and 8192 blocks.
-        // The dispatcher thread alone sets and clears the busy flags.
+        // lone wave on a long tile is latency bound) and one beside others pays
+        // fewer key expansions; between one step and 8192 blocks.  The tiles go
+        // to as many workgroups as there are CUs, one on each that is free: with
+        // one workgroup for every 4 or 16 tiles p50 and p99 were the same at
+        // every load.  The dispatcher thread alone sets and clears the busy flags.
         uint64_t blocks = 0;
         for (const Req &r : slot.reqs) blocks += r.n / 16;
         const uint64_t step = 64ull * s->cfg.blocks_per_lane;
