@@ -1404,22 +1404,30 @@ namespace {
 // at a time (lengths are 1 .. tile_blocks <= 2^24): with 147,071 tiles of up to
 // 4096 blocks build_tiles() took 3.0 ms, 5.7 with a comparison sort, with
 // 9,436 tiles 125 us and 276.  The comparison sort stays for a few tiles, for
-// which clearing the counts (32 KiB) would be most of the work.
-void sort_longest_first(std::vector<Tile> &t, uint32_t tile_blocks) {
-    if (t.size() < 1024) {
-        std::stable_sort(t.begin(), t.end(),
-                         [](const Tile &a, const Tile &b) { return a.n_blocks > b.n_blocks; });
-        return;
+// which clearing the counts (32 KiB) would be most of the work, and where there is
+// no memory for a second copy, which it can do without.
+bool deal_longest_first(std::vector<Tile> &t, uint32_t tile_blocks) {
+    std::vector<Tile> to;
+    try {
+        to.resize(t.size());
+    } catch (const std::bad_alloc &) {
+        return false;
     }
-    std::vector<Tile> to(t.size());
     for (uint32_t shift = 0; shift == 0 || (tile_blocks - 1) >> shift; shift += 12) {
         auto digit = [&](const Tile &x) { return ((tile_blocks - x.n_blocks) >> shift) & 4095u; };
-        std::vector<size_t> at(4097, 0);
+        size_t at[4097] = {};
         for (const Tile &x : t) ++at[digit(x) + 1];
-        for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+        for (size_t i = 1; i < 4097; ++i) at[i] += at[i - 1];
         for (const Tile &x : t) to[at[digit(x)]++] = x;
         t.swap(to);
     }
+    return true;
+}
+
+void sort_longest_first(std::vector<Tile> &t, uint32_t tile_blocks) {
+    if (t.size() >= 1024 && deal_longest_first(t, tile_blocks)) return;
+    std::stable_sort(t.begin(), t.end(),
+                     [](const Tile &a, const Tile &b) { return a.n_blocks > b.n_blocks; });
 }
 
 }  // namespace
